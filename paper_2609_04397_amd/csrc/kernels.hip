@@ -524,14 +524,31 @@ __global__ void __launch_bounds__(kThreads) k_spmm_vp(FwdParams<T> P) {
 // ---------------------------------------------------------------------------
 // A operand: the panel's 4-column slice (contiguous, 4*b values, panel row m
 // in lane m, slice column kq in lane group kq); B operand: the X rows of
-// those 4 columns.  Slices are taken in groups of U.  Two register sets
-// alternate: while one group multiplies, the values and X rows of the next
-// group and the column indices of the one after are in flight.  The loop
-// has no data-dependent branch (a branch around a load makes the compiler
-// wait for every load in flight): values and indices are buffer loads that
-// read zero past the panel, and padding slices point at a row of zeros
-// instead of a row of X.  Scheduling barriers keep each group's loads ahead
-// of the previous group's matrix instructions.
+// those 4 columns.  Slices are taken in groups of U.  A ring of R register
+// sets: while one group multiplies, the values and X rows of the next R - 1
+// groups are in flight, and the column indices of the R after those.  The
+// ring loop has no branch (one around a load, or a way out of the loop other
+// than its end, makes the compiler copy the sets and wait for every load in
+// flight); the last groups are multiplied after it.  Values and indices are
+// buffer loads that read zero past the panel, and padding slices point at a
+// row of zeros instead of a row of X.  An index is compared with the panel's
+// end where it is used, not where it is loaded: done at the load, it makes
+// every group wait for the index just requested and, since loads return in
+// order, for all the X rows requested before it.  Scheduling barriers keep
+// each group's loads ahead of the matrix instructions.
+//
+// What bounds it: the compute unit's load path.  A load instruction of 8 or
+// 16 bytes a lane takes 16 cycles of it, one of 4 bytes 4.7, and the value
+// stream from HBM and the gathered rows from L2 return through it in order,
+// so their times add up (5 KiB of L2 hits alone take 102 cycles of a unit,
+// 1 KiB of stream alone 95, together 221, at any occupancy).  Against two
+// alternating sets with the index tested at the load: FP64 1,000 atoms of
+// b = 4/9, nrhs 16: 14.8 -> 12.1 us a call; FP64 50,000 atoms of b = 1/4/9,
+// nrhs 32: 219 -> 202 us; FP64 Chebyshev step on the 24^3 lattice b = 13,
+// nrhs 64: 206 -> 201 us; FP32 nrhs 64 on the 40,000-atom particle 326 ->
+// 320 us; FP32 nrhs 32 on the small blocks level.  Longer rings (R = 4)
+// gain 2 % on the lattice and lose 4 % on the small blocks, groups of one
+// slice lose on the lattice.
 //
 // Fast path (VX = true): the N index of the 16x16 tiles is permuted so that
 // lane m of tile t holds right-hand side c0 + l*16*VEC + VEC*m + e, with
@@ -551,7 +568,8 @@ __global__ void __launch_bounds__(kThreads) k_spmm_mfma(FwdParams<T> P) {
   using L16 = typename Vec16<T>::type;
   constexpr int VEC = Vec16<T>::n;
   constexpr int NL = VX ? NT / VEC : 0;  // 16-byte loads per lane and X row
-  constexpr int U = NT * sizeof(T) >= 32 ? 2 : 4;  // slices per group
+  constexpr int U = 2;                    // slices per group
+  constexpr int R = NT * sizeof(T) <= 8 ? 4 : 3;  // groups in the ring
   static_assert(!VX || NT % VEC == 0, "tile count must fill whole 16-byte loads");
   const int wg = xcd_remap(blockIdx.x, gridDim.x);
   const int w = wave_id();
@@ -592,8 +610,7 @@ __global__ void __launch_bounds__(kThreads) k_spmm_mfma(FwdParams<T> P) {
 #pragma unroll
           for (int u = 0; u < U; ++u) {
             const int k = (g * U + u) * 4 + kq;
-            const int32_t v = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(rc, (uint32_t)k * 4, 0, 0);
-            xi[u] = k < K ? v : -1;
+            xi[u] = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(rc, (uint32_t)k * 4, 0, 0);
           }
         };
         auto ld_val = [&](int g, T(&av)[U]) {
@@ -601,13 +618,14 @@ __global__ void __launch_bounds__(kThreads) k_spmm_mfma(FwdParams<T> P) {
           for (int u = 0; u < U; ++u)
             av[u] = buf_load_nt<T>(rv, vlane + (uint32_t)((g * U + u) * 4 * b) * sizeof(T));
         };
-        auto ld_x = [&](const int32_t(&xi)[U], T(&xv)[U][NT]) {
+        auto ld_x = [&](int g, const int32_t(&xi)[U], T(&xv)[U][NT]) {
 #pragma unroll
           for (int u = 0; u < U; ++u) {
+            const bool kin = (g * U + u) * 4 + kq < K;
             if constexpr (XB) {
               // padding slices read past the descriptor: zeros
               const uint32_t ro =
-                  xi[u] >= 0 ? (uint32_t)((int64_t)xi[u] * P.ldx * (int64_t)sizeof(T)) + xcol : kOut;
+                  kin ? (uint32_t)((int64_t)xi[u] * P.ldx * (int64_t)sizeof(T)) + xcol : kOut;
               if constexpr (VX) {
 #pragma unroll
                 for (int l = 0; l < (VX ? NL : 1); ++l) {
@@ -624,7 +642,7 @@ __global__ void __launch_bounds__(kThreads) k_spmm_mfma(FwdParams<T> P) {
               }
             } else {
               // padding slices read a row of zeros instead of a row of X
-              const T *xp = xi[u] >= 0 ? P.X + (int64_t)xi[u] * P.ldx + c0 : zero_row<T>();
+              const T *xp = kin ? P.X + (int64_t)xi[u] * P.ldx + c0 : zero_row<T>();
               if constexpr (VX) {
 #pragma unroll
                 for (int l = 0; l < (VX ? NL : 1); ++l) {
@@ -650,27 +668,33 @@ __global__ void __launch_bounds__(kThreads) k_spmm_mfma(FwdParams<T> P) {
             for (int t = 0; t < NT; ++t) acc[t] = mfma(av[u], xv[u][t], acc[t]);
         };
         const int ngroups = (nsteps + U - 1) / U;
-        T aA[U], aB[U], vA[U][NT], vB[U][NT];
-        int32_t iA[U], iB[U];
-        ld_idx(0, iA);
-        ld_idx(1, iB);
-        ld_x(iA, vA);
-        ld_val(0, aA);
-        for (int g = 0; g < ngroups; g += 2) {
-          ld_idx(g + 2, iA);
-          ld_x(iB, vB);
-          ld_val(g + 1, aB);
-          __builtin_amdgcn_sched_barrier(0);
-          mma(aA, vA);
-          __builtin_amdgcn_sched_barrier(0);
-          if (g + 1 >= ngroups) break;
-          ld_idx(g + 3, iB);
-          ld_x(iA, vA);
-          ld_val(g + 2, aA);
-          __builtin_amdgcn_sched_barrier(0);
-          mma(aB, vB);
-          __builtin_amdgcn_sched_barrier(0);
+        T av[R][U], xv[R][U][NT];
+        int32_t xi[R][U];
+#pragma unroll
+        for (int r = 0; r < R; ++r) ld_idx(r, xi[r]);
+#pragma unroll
+        for (int r = 0; r + 1 < R; ++r) {
+          ld_x(r, xi[r], xv[r]);
+          ld_val(r, av[r]);
+          ld_idx(r + R, xi[r]);
         }
+        __builtin_amdgcn_sched_barrier(0);
+        int g = 0;
+        for (; g + R <= ngroups; g += R) {
+#pragma unroll
+          for (int r = 0; r < R; ++r) {
+            const int q = (r + R - 1) % R;
+            ld_x(g + r + R - 1, xi[q], xv[q]);
+            ld_val(g + r + R - 1, av[q]);
+            ld_idx(g + r + 2 * R - 1, xi[q]);
+            __builtin_amdgcn_sched_barrier(0);
+            mma(av[r], xv[r]);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+#pragma unroll
+        for (int r = 0; r + 1 < R; ++r)
+          if (g + r < ngroups) mma(av[r], xv[r]);
         // epilogue: row pr of the tile, columns col(t)
         double mmv[NT];
 #pragma unroll
