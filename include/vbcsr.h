@@ -32,6 +32,11 @@
  * vbcsr_set_values, vbcsr_use_pages and vbcsr_refresh_transposed;
  * products on different streams may run concurrently on one handle, but
  * must not overlap a vbcsr_set_values on it.
+ *
+ * Device memory: blocks of destroyed vbcsr_mat handles and of calls'
+ * temporaries are kept for later calls, at most 1/64 of the device's memory,
+ * while the library holds other memory on the device; they are returned when
+ * an allocation fails and with the last handle.
  */
 #ifndef VBCSR_H
 #define VBCSR_H

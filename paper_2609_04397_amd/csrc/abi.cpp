@@ -9,10 +9,13 @@
 #include <cstdlib>
 #include <cstring>
 #include <memory>
+#include <mutex>
 #include <new>
 #include <stdexcept>
 #include <string>
 #include <system_error>
+#include <unordered_map>
+#include <vector>
 
 #include "../../include/vbcsr.h"
 #include "common.hpp"
@@ -82,19 +85,136 @@ int hip_fail(hipError_t e, const char *where) {
 // HIP call is made.
 std::atomic<long> g_alloc_count{0};
 
+// Device blocks given back by handles and calls, kept for the next ones: a
+// hipMalloc and hipFree of the block product's results and temporaries cost
+// far more than its kernels (C = A A of 5,760 atoms with b in 9..20, 2.8 GB,
+// read back and destroyed, pass after pass: 92 ms with them, 5.5 ms without,
+// of which the kernels take 4.9).
+//   * A block is kept only once nothing on its device can still use it (the
+//     callers of dev_free have synchronised the device), so it may go to any
+//     stream and thread.  Contents are never relied on.
+//   * At most 1/64 of the device's memory (4.5 GB here) is kept, the oldest
+//     blocks going first; all of it is returned when an allocation fails and
+//     when the library holds no other block on the device.
+//   * A request takes the smallest kept block that is at most a quarter (or
+//     1 MiB) larger than it.
+struct DevCache {
+  struct Block {
+    void *p;
+    size_t bytes;
+    int dev;
+  };
+  std::mutex mu;
+  std::vector<Block> kept;                              // oldest first
+  std::unordered_map<void *, Block> out;                // handed out
+  std::unordered_map<int, size_t> limit, held, n_out;   // per device
+
+  void release(int dev, size_t over) {   // free kept blocks of dev until held <= over
+    for (size_t i = 0; i < kept.size() && held[dev] > over;) {
+      if (kept[i].dev != dev) {
+        ++i;
+        continue;
+      }
+      held[dev] -= kept[i].bytes;
+      (void)hipFree(kept[i].p);
+      kept.erase(kept.begin() + (std::ptrdiff_t)i);
+    }
+  }
+};
+DevCache &dev_cache() {
+  static DevCache *c = new DevCache;   // never destroyed: handles may outlive static objects
+  return *c;
+}
+
 int dev_alloc(void **p, size_t bytes) {
   *p = nullptr;
   const char *lim = std::getenv("VBCSR_FAIL_ALLOC_AFTER");
   const long n = g_alloc_count.fetch_add(1);
   if (lim && *lim && n >= std::atol(lim)) return fail(VBCSR_ENOMEM, "injected allocation failure");
   if (bytes == 0) return VBCSR_OK;
-  hipError_t e = hipMalloc(p, bytes);
-  if (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation) {
-    (void)hipGetLastError();
-    return fail(VBCSR_ENOMEM, "hipMalloc of " + std::to_string(bytes) + " bytes failed");
+  int dev = 0;
+  HIP_TRY(hipGetDevice(&dev), "hipGetDevice");
+  DevCache &c = dev_cache();
+  std::lock_guard<std::mutex> lock(c.mu);
+  size_t best = c.kept.size();
+  for (size_t i = 0; i < c.kept.size(); ++i) {
+    const DevCache::Block &k = c.kept[i];
+    if (k.dev == dev && k.bytes >= bytes && k.bytes - bytes <= std::max<size_t>(bytes / 4, 1 << 20) &&
+        (best == c.kept.size() || k.bytes < c.kept[best].bytes))
+      best = i;
   }
-  if (e != hipSuccess) return hip_fail(e, "hipMalloc");
+  DevCache::Block blk{nullptr, bytes, dev};
+  const bool reuse = best < c.kept.size();
+  if (reuse) blk = c.kept[best];
+  // room for the bookkeeping first: nothing below it can throw
+  auto slot = c.out.end();
+  if (!reuse) {
+    hipError_t e = hipMalloc(&blk.p, bytes);
+    if (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation) {
+      (void)hipGetLastError();
+      c.release(dev, 0);
+      e = hipMalloc(&blk.p, bytes);
+    }
+    if (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation) {
+      (void)hipGetLastError();
+      return fail(VBCSR_ENOMEM, "hipMalloc of " + std::to_string(bytes) + " bytes failed");
+    }
+    if (e != hipSuccess) return hip_fail(e, "hipMalloc");
+  }
+  try {
+    c.held[dev];
+    c.n_out[dev];
+    slot = c.out.emplace(blk.p, blk).first;
+  } catch (...) {
+    if (!reuse) (void)hipFree(blk.p);
+    throw;
+  }
+  if (reuse) {
+    c.held[dev] -= blk.bytes;
+    c.kept.erase(c.kept.begin() + (std::ptrdiff_t)best);
+  }
+  ++c.n_out[dev];
+  *p = slot->first;
   return VBCSR_OK;
+}
+
+// Give back a block of dev_alloc.  `idle`: the caller has synchronised the
+// current device since the block's last use; otherwise (and for a block of
+// another device) it is freed, which waits by itself.
+void dev_free(void *p, bool idle) noexcept {
+  if (!p) return;
+  int cur = -1;
+  (void)hipGetDevice(&cur);
+  DevCache &c = dev_cache();
+  std::lock_guard<std::mutex> lock(c.mu);
+  const auto it = c.out.find(p);
+  if (it == c.out.end()) {
+    (void)hipFree(p);
+    return;
+  }
+  const DevCache::Block blk = it->second;
+  c.out.erase(it);
+  const size_t left = --c.n_out[blk.dev];
+  bool keep = idle && blk.dev == cur && left > 0;
+  if (keep) {
+    try {
+      size_t &lim = c.limit[blk.dev];
+      if (lim == 0) {
+        size_t avail = 0, total = 0;
+        lim = hipMemGetInfo(&avail, &total) == hipSuccess ? std::max<size_t>(total / 64, 1) : 1;
+      }
+      keep = blk.bytes <= lim;
+      if (keep) {
+        c.release(blk.dev, lim - blk.bytes);
+        c.kept.push_back(blk);
+        c.held[blk.dev] += blk.bytes;
+      }
+    } catch (...) {
+      keep = false;
+    }
+  }
+  if (!keep) (void)hipFree(blk.p);
+  if (left == 0) c.release(blk.dev, 0);
 }
 
 template <typename T>
@@ -186,8 +306,8 @@ int upload_into(vbcsr_mat *A, T **p, const std::vector<T, Alloc> &v, hipStream_t
 
 void free_all(vbcsr_mat *A) {
   if (!A) return;
-  if (!A->owned.empty()) (void)hipDeviceSynchronize();
-  for (void *p : A->owned) (void)hipFree(p);
+  const bool idle = A->owned.empty() || hipDeviceSynchronize() == hipSuccess;
+  for (void *p : A->owned) dev_free(p, idle);
   A->owned.clear();
 }
 
@@ -464,7 +584,7 @@ int create_impl(vbcsr_mat **out, int32_t n_atoms, const int32_t *block_sizes,
       rc = pack_all(A, stage, 0, s);
       e = hipStreamSynchronize(s);
     }
-    (void)hipFree(stage);
+    dev_free(stage, e == hipSuccess);
     if (rc) return bail(rc);
     if (e != hipSuccess) return bail(hip_fail(e, "create"));
   } else {
@@ -564,8 +684,8 @@ int create_planned_on_device(vbcsr_mat **out, const vbcsr_mat *A, int64_t nnzb, 
 }
 
 
-// Device allocations that live for one call; freed (after the stream has
-// been synchronised by the caller) when the object goes out of scope.
+// Device allocations that live for one call; given back, after a device
+// synchronisation, when the object goes out of scope.
 struct TempAllocs {
   std::vector<void *> ptrs;
   template <typename T>
@@ -581,7 +701,8 @@ struct TempAllocs {
     return rc;
   }
   ~TempAllocs() {
-    for (void *p : ptrs) (void)hipFree(p);
+    const bool idle = ptrs.empty() || hipDeviceSynchronize() == hipSuccess;
+    for (void *p : ptrs) dev_free(p, idle);
   }
 };
 
@@ -686,7 +807,7 @@ int vbcsr_set_values(vbcsr_mat *A, const void *values, int on_device, int dtype,
     rc = pack_all(A, stage, dtype, s);
     e = hipStreamSynchronize(s);
   }
-  (void)hipFree(stage);
+  dev_free(stage, e == hipSuccess);
   if (rc) return rc;
   if (e != hipSuccess) return hip_fail(e, "set_values");
   return VBCSR_OK;
@@ -819,9 +940,9 @@ int vbcsr_refresh_transposed(vbcsr_mat *A, void *stream) try {
       e = launch_refresh_records(pp, order, recs, s);
     }
     if (e == hipSuccess) e = hipStreamSynchronize(s);
-    for (void *q : tmp) (void)hipFree(q);
+    for (void *q : tmp) dev_free(q, e == hipSuccess);
     if (e != hipSuccess) {
-      (void)hipFree(recs);
+      dev_free(recs, false);
       return hip_fail(e, "page records");
     }
     A->owned.push_back(recs);
@@ -951,7 +1072,7 @@ int vbcsr_cheb_moments(const vbcsr_mat *A, const void *R, int64_t ldr, int32_t n
   if (e == hipSuccess && rc == VBCSR_OK)
     e = hipMemcpyAsync(mu.data(), all_mu, sizeof(double) * mu.size(), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
-  if (!workspace) (void)hipFree(ws);
+  if (!workspace) dev_free(ws, e == hipSuccess && rc == VBCSR_OK);
   if (rc) return rc;
   if (e != hipSuccess) return hip_fail(e, "cheb_moments");
   std::copy(mu.begin(), mu.end(), mu_host);
@@ -1034,7 +1155,7 @@ int vbcsr_cheb_moments_doubled(const vbcsr_mat *A, const void *R, int64_t ldr, i
   if (e == hipSuccess && rc == VBCSR_OK)
     e = hipMemcpyAsync(r.data(), raw, sizeof(double) * r.size(), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
-  if (!workspace) (void)hipFree(ws);
+  if (!workspace) dev_free(ws, e == hipSuccess && rc == VBCSR_OK);
   if (rc) return rc;
   if (e != hipSuccess) return hip_fail(e, "cheb_moments_doubled");
   // mu_0 = <R,R>, mu_1 = <R,T_1>, mu_2k = 2<T_k,T_k> - mu_0, mu_2k+1 = 2<T_k,T_k+1> - mu_1
