@@ -1820,15 +1820,37 @@ __global__ void __launch_bounds__(kThreads) k_sddmm_dma32(SddmmParams<float> P) 
 // ---------------------------------------------------------------------------
 constexpr int kDotRows = 256;
 
-template <typename T>
+// One workgroup per kDotRows rows.  The threads form CL columns (the power of
+// two at or above nrhs, at most 64) by kThreads / CL rows, so that every lane
+// has work and every load of a wave is one run of row pieces; the row lanes'
+// sums meet in LDS in a fixed order.  SAME: B is A, read once.  (With one
+// thread per column three waves of four idled: <A, A> of 425,984 rows x 64
+// floats 77 us, now 17.6, 6.2 TB/s.)
+template <typename T, bool SAME>
 __global__ void __launch_bounds__(kThreads) k_coldot(const T *A, int64_t lda, const T *B, int64_t ldb,
-                                                     int64_t nrows, int32_t nrhs, double *partial) {
+                                                     int64_t nrows, int32_t nrhs, int cl,
+                                                     double *partial) {
+  __shared__ double s[kThreads];
   const int64_t r0 = (int64_t)blockIdx.x * kDotRows;
   const int64_t r1 = min(r0 + kDotRows, nrows);
-  for (int c = threadIdx.x; c < nrhs; c += kThreads) {
+  const int tc = threadIdx.x & (cl - 1), tr = threadIdx.x / cl, nr = kThreads / cl;
+  for (int c0 = 0; c0 < nrhs; c0 += cl) {
+    const int c = c0 + tc;
     double t = 0.0;
-    for (int64_t r = r0; r < r1; ++r) t += (double)A[r * lda + c] * (double)B[r * ldb + c];
-    partial[(int64_t)blockIdx.x * nrhs + c] = t;
+    if (c < nrhs) {
+#pragma unroll 8
+      for (int64_t r = r0 + tr; r < r1; r += nr) {
+        const double a = (double)A[r * lda + c];
+        t += a * (SAME ? a : (double)B[r * ldb + c]);
+      }
+    }
+    s[threadIdx.x] = t;
+    __syncthreads();
+    if (tr == 0 && c < nrhs) {
+      for (int q = 1; q < nr; ++q) t += s[q * cl + tc];
+      partial[(int64_t)blockIdx.x * nrhs + c] = t;
+    }
+    __syncthreads();
   }
 }
 
@@ -2319,25 +2341,36 @@ hipError_t launch_sddmm_f32(const SddmmParams<float> &p, hipStream_t s) {
   return launch_sddmm_t(p, s);
 }
 
+static int dot_columns(int32_t nrhs) {
+  int cl = 1;
+  while (cl < 64 && cl < nrhs) cl *= 2;
+  return cl;
+}
 int64_t coldot_chunks(int64_t nrows) { return (nrows + kDotRows - 1) / kDotRows; }
 
+template <typename T>
+hipError_t launch_coldot_t(const T *A, int64_t lda, const T *B, int64_t ldb, int64_t nrows,
+                           int32_t nrhs, double *partial, int64_t *nchunks, hipStream_t s) {
+  *nchunks = coldot_chunks(nrows);
+  if (*nchunks == 0) return hipSuccess;
+  const dim3 grid((unsigned)*nchunks);
+  if (A == B && lda == ldb)
+    hipLaunchKernelGGL((k_coldot<T, true>), grid, dim3(kThreads), 0, s, A, lda, B, ldb, nrows, nrhs,
+                       dot_columns(nrhs), partial);
+  else
+    hipLaunchKernelGGL((k_coldot<T, false>), grid, dim3(kThreads), 0, s, A, lda, B, ldb, nrows,
+                       nrhs, dot_columns(nrhs), partial);
+  return hipGetLastError();
+}
 hipError_t launch_coldot_f64(const double *A, int64_t lda, const double *B, int64_t ldb,
                              int64_t nrows, int32_t nrhs, double *partial, int64_t *nchunks,
                              hipStream_t s) {
-  *nchunks = coldot_chunks(nrows);
-  if (*nchunks == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_coldot<double>, dim3((unsigned)*nchunks), dim3(kThreads), 0, s, A, lda, B,
-                     ldb, nrows, nrhs, partial);
-  return hipGetLastError();
+  return launch_coldot_t(A, lda, B, ldb, nrows, nrhs, partial, nchunks, s);
 }
 hipError_t launch_coldot_f32(const float *A, int64_t lda, const float *B, int64_t ldb,
                              int64_t nrows, int32_t nrhs, double *partial, int64_t *nchunks,
                              hipStream_t s) {
-  *nchunks = coldot_chunks(nrows);
-  if (*nchunks == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_coldot<float>, dim3((unsigned)*nchunks), dim3(kThreads), 0, s, A, lda, B,
-                     ldb, nrows, nrhs, partial);
-  return hipGetLastError();
+  return launch_coldot_t(A, lda, B, ldb, nrows, nrhs, partial, nchunks, s);
 }
 
 hipError_t launch_reduce_partials(const double *partial, int64_t nparts, int32_t nrhs, double *out,
