@@ -154,6 +154,20 @@ template <> __device__ __forceinline__ float buf_load<float>(__amdgpu_buffer_rsr
   return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
 }
 
+// Bytes from X's first element to its last (XB kernels: below 2^31).
+template <typename T> __device__ __forceinline__ uint32_t x_span(const FwdParams<T> &P) {
+  return P.xrows > 0
+             ? (uint32_t)(((P.xrows - 1) * P.ldx + P.nrhs) * (int64_t)sizeof(T))
+             : 0u;
+}
+
+// Value of lane 16 q + U of the caller's 16-lane row q, to the whole row.
+template <int U>
+__device__ __forceinline__ int32_t row_bcast(int32_t v) {
+  // 0x150 + n: row_newbcast of the gfx9 data-parallel primitives
+  return __builtin_amdgcn_update_dpp(0, v, 0x150 + U, 0xF, 0xF, false);
+}
+
 // 64 zeros, read in place of an X row where a lane has none (padding slices,
 // columns past a staged chunk, right-hand sides past nrhs); any T of <= 8 bytes
 __device__ __align__(16) double kZeroRow[64] = {};  // never written
@@ -538,15 +552,18 @@ __global__ void __launch_bounds__(kThreads) k_spmm_vp(FwdParams<T> P) {
 // each group's loads ahead of the matrix instructions.
 //
 // What bounds it: the compute unit's load path.  A load instruction of 8 or
-// 16 bytes a lane takes 16 cycles of it, one of 4 bytes 4.7, and the value
-// stream from HBM and the gathered rows from L2 return through it in order,
-// so their times add up (5 KiB of L2 hits alone take 102 cycles of a unit,
-// 1 KiB of stream alone 95, together 221, at any occupancy).  Against two
-// alternating sets with the index tested at the load: FP64 1,000 atoms of
-// b = 4/9, nrhs 16: 14.8 -> 12.1 us a call; FP64 50,000 atoms of b = 1/4/9,
-// nrhs 32: 219 -> 202 us; FP64 Chebyshev step on the 24^3 lattice b = 13,
-// nrhs 64: 206 -> 201 us; FP32 nrhs 64 on the 40,000-atom particle 326 ->
-// 320 us; FP32 nrhs 32 on the small blocks level.  Longer rings (R = 4)
+// 16 bytes a lane takes 16 cycles of it; one of 4 bytes takes 4.7 when every
+// four neighbouring lanes read consecutive or equal addresses, and 16 too
+// when they don't or only some of them are in range.  The value stream from
+// HBM and the gathered rows from L2 return through it in order, so their
+// times add up (5 KiB of L2 hits alone take 102 cycles of a unit, 1 KiB of
+// stream alone 95, together 221, at any occupancy).  Measured against two
+// alternating sets with the index tested at the load and masked rows and
+// right-hand sides: FP32 100,000 atoms of b = 1/4/9, nrhs 32: 269 -> 231 us;
+// FP32 40,000-atom particle, nrhs 13: 276 -> 159, nrhs 33: 371 -> 267, nrhs
+// 64: 326 -> 299; FP64 1,000 atoms of b = 4/9, nrhs 16: 14.8 -> 11.7 us a
+// call; FP64 50,000 atoms of b = 1/4/9, nrhs 32: 220 -> 195; FP64 Chebyshev
+// step on the 24^3 lattice b = 13, nrhs 64: 206 -> 200.  Longer rings (R = 4)
 // gain 2 % on the lattice and lose 4 % on the small blocks, groups of one
 // slice lose on the lattice.
 //
@@ -590,7 +607,6 @@ __global__ void __launch_bounds__(kThreads) k_spmm_mfma(FwdParams<T> P) {
     };
     for (int mt = 0; mt * 16 < b; ++mt) {
       const int p = mt * 16 + m;
-      const bool prow = p < b;
       for (int c0 = 0; c0 < P.nrhs; c0 += 16 * NT) {
         V acc[NT];
 #pragma unroll
@@ -600,32 +616,51 @@ __global__ void __launch_bounds__(kThreads) k_spmm_mfma(FwdParams<T> P) {
         constexpr uint32_t kOut = 0x80000000u;
         const __amdgpu_buffer_rsrc_t rv = panel_rsrc(vals, (uint32_t)((int64_t)K * b * sizeof(T)));
         const __amdgpu_buffer_rsrc_t rc = panel_rsrc(cx, (uint32_t)(K * 4));
-        const uint32_t vlane = prow ? (uint32_t)(kq * b + p) * sizeof(T) : kOut;
+        // Rows past the panel: 4-byte loads read the next column's values
+        // into tile rows that are never stored, since four neighbouring lanes
+        // of which some are out of range take the slow path of the load unit
+        // (16 cycles instead of 4.7; FP32 nrhs 32 on the small blocks 285 ->
+        // 240 us); 8-byte loads cost 16 cycles anyway and stay masked.
+        const uint32_t vlane =
+            sizeof(T) == 4 || p < b ? (uint32_t)(kq * b + p) * sizeof(T) : kOut;
         // XB: all of X lies within 2^31 bytes and is read through one buffer
         // descriptor (cheaper addressing); otherwise through 64-bit pointers
         const __amdgpu_buffer_rsrc_t rx =
-            panel_rsrc(P.X, XB ? (uint32_t)(P.xrows * P.ldx * (int64_t)sizeof(T)) : 0u);
+            panel_rsrc(P.X, XB ? x_span(P) : 0u);
         const uint32_t xcol = (uint32_t)(c0 + (VX ? VEC * m : m)) * sizeof(T);
-        auto ld_idx = [&](int g, int32_t(&xi)[U]) {
-#pragma unroll
-          for (int u = 0; u < U; ++u) {
-            const int k = (g * U + u) * 4 + kq;
-            xi[u] = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(rc, (uint32_t)k * 4, 0, 0);
-          }
+        // lane (m, kq) loads the index of column kq of slice m / 8 (equal
+        // addresses in every group of four lanes); the lanes of a row (equal
+        // kq) then read slice u's from lane 8 u
+        static_assert(U == 2, "one index register serves two slices");
+        auto ld_idx = [&](int g) {
+          const int k = (g * U + (m >> 3)) * 4 + kq;
+          return (int32_t)__builtin_amdgcn_raw_buffer_load_b32(rc, (uint32_t)k * 4, 0, 0);
         };
+        // 4-byte loads of right-hand sides: four neighbouring lanes are in
+        // range together (see the values above); those past nrhs read what
+        // follows inside X's span into output columns that are never stored
+        const int mq = sizeof(T) == 4 ? m & ~3 : m;
         auto ld_val = [&](int g, T(&av)[U]) {
 #pragma unroll
           for (int u = 0; u < U; ++u)
             av[u] = buf_load_nt<T>(rv, vlane + (uint32_t)((g * U + u) * 4 * b) * sizeof(T));
         };
-        auto ld_x = [&](int g, const int32_t(&xi)[U], T(&xv)[U][NT]) {
+        auto ld_x = [&](int g, int32_t xg, T(&xv)[U][NT]) {
+          // XB: byte offset of the lane's own column, past the descriptor for
+          // a padding column (reads zeros).  The product is formed before the
+          // broadcast: after it the compiler fuses it with the addition of
+          // xcol into a 64-bit one whose unused upper half can be a register
+          // with a load in flight, and waits for that load.
+          const int32_t xo =
+              XB ? ((g * U + (m >> 3)) * 4 + kq < K
+                        ? (int32_t)(uint32_t)((int64_t)xg * P.ldx * (int64_t)sizeof(T))
+                        : (int32_t)kOut)
+                 : xg;
+          const int32_t xi[U] = {row_bcast<0>(xo), row_bcast<8>(xo)};
 #pragma unroll
           for (int u = 0; u < U; ++u) {
-            const bool kin = (g * U + u) * 4 + kq < K;
             if constexpr (XB) {
-              // padding slices read past the descriptor: zeros
-              const uint32_t ro =
-                  kin ? (uint32_t)((int64_t)xi[u] * P.ldx * (int64_t)sizeof(T)) + xcol : kOut;
+              const uint32_t ro = (uint32_t)xi[u] + xcol;
               if constexpr (VX) {
 #pragma unroll
                 for (int l = 0; l < (VX ? NL : 1); ++l) {
@@ -638,11 +673,11 @@ __global__ void __launch_bounds__(kThreads) k_spmm_mfma(FwdParams<T> P) {
               } else {
 #pragma unroll
                 for (int t = 0; t < NT; ++t)
-                  xv[u][t] = buf_load<T>(rx, c0 + t * 16 + m < P.nrhs ? ro + t * 16 * sizeof(T) : kOut);
+                  xv[u][t] = buf_load<T>(rx, c0 + t * 16 + mq < P.nrhs ? ro + t * 16 * sizeof(T) : kOut);
               }
             } else {
               // padding slices read a row of zeros instead of a row of X
-              const T *xp = kin ? P.X + (int64_t)xi[u] * P.ldx + c0 : zero_row<T>();
+              const T *xp = (g * U + u) * 4 + kq < K ? P.X + (int64_t)xi[u] * P.ldx + c0 : zero_row<T>();
               if constexpr (VX) {
 #pragma unroll
                 for (int l = 0; l < (VX ? NL : 1); ++l) {
@@ -669,14 +704,14 @@ __global__ void __launch_bounds__(kThreads) k_spmm_mfma(FwdParams<T> P) {
         };
         const int ngroups = (nsteps + U - 1) / U;
         T av[R][U], xv[R][U][NT];
-        int32_t xi[R][U];
+        int32_t xi[R];
 #pragma unroll
-        for (int r = 0; r < R; ++r) ld_idx(r, xi[r]);
+        for (int r = 0; r < R; ++r) xi[r] = ld_idx(r);
 #pragma unroll
         for (int r = 0; r + 1 < R; ++r) {
           ld_x(r, xi[r], xv[r]);
           ld_val(r, av[r]);
-          ld_idx(r + R, xi[r]);
+          xi[r] = ld_idx(r + R);
         }
         __builtin_amdgcn_sched_barrier(0);
         int g = 0;
@@ -686,7 +721,7 @@ __global__ void __launch_bounds__(kThreads) k_spmm_mfma(FwdParams<T> P) {
             const int q = (r + R - 1) % R;
             ld_x(g + r + R - 1, xi[q], xv[q]);
             ld_val(g + r + R - 1, av[q]);
-            ld_idx(g + r + 2 * R - 1, xi[q]);
+            xi[q] = ld_idx(g + r + 2 * R - 1);
             __builtin_amdgcn_sched_barrier(0);
             mma(av[r], xv[r]);
             __builtin_amdgcn_sched_barrier(0);
@@ -763,10 +798,35 @@ __global__ void __launch_bounds__(kThreads) k_spmm_mfma(FwdParams<T> P) {
 // ---------------------------------------------------------------------------
 // 32-column slices; lane (m, kg) owns 8 consecutive panel columns of row m
 // (one 16-byte load per page) and, for the B operand, the same 8 columns of
-// X in column m of the tile.  X is split into bf16 hi/lo on the fly.  Loads
-// are branch-free and the next slice's values and indices are in flight
-// while the current slice multiplies.
-template <int NT, bool MOM>
+// X in column m of the tile.  X is split into bf16 hi/lo on the fly with the
+// hardware round-to-nearest-even conversion (two values per instruction).
+// Loads are branch-free and the next slice's values and X rows are in flight
+// while the current slice multiplies, its column indices two slices ahead.
+typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ unsigned int pack_bf16(float a, float b) {
+  return __builtin_bit_cast(unsigned int, v2bf{(__bf16)a, (__bf16)b});
+}
+
+// Split of 8 consecutive panel columns' X values into hi and lo fragments.
+__device__ __forceinline__ void split_bf16(const float (&x)[8], v8u &xh, v8u &xl) {
+  v4u32 hi, lo;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const unsigned int h = pack_bf16(x[2 * q], x[2 * q + 1]);
+    hi[q] = h;
+    lo[q] = pack_bf16(x[2 * q] - __uint_as_float(h << 16),
+                      x[2 * q + 1] - __uint_as_float(h & 0xFFFF0000u));
+  }
+  xh = __builtin_bit_cast(v8u, hi);
+  xl = __builtin_bit_cast(v8u, lo);
+}
+
+// Any nrhs and leading dimension, NT tiles of 16 right-hand sides per pass,
+// one 4-byte load per lane, X row and tile.  (With clamped pointer loads and
+// a software rounding, waiting for each slice's X rows: nrhs 32 on 100,000
+// atoms of b = 1/4/9 788 us, now 208; nrhs 50 on the 40,000-atom particle
+// 1186 -> 300, nrhs 20 550 -> 163.)
+template <int NT, bool MOM, bool XB>
 __global__ void __launch_bounds__(kThreads) k_spmm_bf16x3(FwdParams<float> P) {
   extern __shared__ double s_mom[];
   const int wg = xcd_remap(blockIdx.x, gridDim.x);
@@ -782,70 +842,91 @@ __global__ void __launch_bounds__(kThreads) k_spmm_bf16x3(FwdParams<float> P) {
     const int ngroups = (K + 7) >> 3;
     const int nsteps = (K + 31) >> 5;
     const int64_t vb16 = P.vbase16[row];
-    const int32_t *__restrict__ cx = P.colx + rd.cbase;
+    constexpr uint32_t kOut = 0x80000000u;
+    const uint32_t pbytes = (uint32_t)((int64_t)ngroups * 8 * b * sizeof(uint16_t));
+    const __amdgpu_buffer_rsrc_t rh = panel_rsrc(P.hi + vb16, pbytes);
+    const __amdgpu_buffer_rsrc_t rl = panel_rsrc(P.lo + vb16, pbytes);
+    const __amdgpu_buffer_rsrc_t rc = panel_rsrc(P.colx + rd.cbase, (uint32_t)(K * 4));
+    const __amdgpu_buffer_rsrc_t rx =
+        panel_rsrc(P.X, XB ? x_span(P) : 0u);
     for (int mt = 0; mt * 16 < b; ++mt) {
       const int p = mt * 16 + m;
-      const bool prow = p < b;
-      const int pc = prow ? p : b - 1;
+      const uint32_t vlane = p < b ? (uint32_t)(kg * 8 * b + p * 8) * sizeof(uint16_t) : kOut;
       for (int c0 = 0; c0 < P.nrhs; c0 += 16 * NT) {
-        int nn[NT];
-        bool nok[NT];
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-          const int n = c0 + t * 16 + m;
-          nok[t] = n < P.nrhs;
-          nn[t] = nok[t] ? n : P.nrhs - 1;
-        }
         v4f acc[NT];
 #pragma unroll
         for (int t = 0; t < NT; ++t) acc[t] = v4f{};
-        auto fetch = [&](int s, v8u &h, v8u &l, int32_t *x) {
-          const int grp = s * 4 + kg;
-          const bool ok = prow && grp < ngroups;
-          const int64_t a = vb16 + (int64_t)min(grp, max(ngroups - 1, 0)) * 8 * b + pc * 8;
-          const v8u hv = stream_load(reinterpret_cast<const v8u *>(P.hi + a));
-          const v8u lv = stream_load(reinterpret_cast<const v8u *>(P.lo + a));
-          h = ok ? hv : v8u{};
-          l = ok ? lv : v8u{};
-#pragma unroll
-          for (int u = 0; u < 8; ++u) x[u] = cx[min(grp * 8 + u, K - 1)];
+        const uint32_t xcol = (uint32_t)(c0 + m) * sizeof(float);
+        auto ld_idx = [&](int s) {
+          // lane (m, kg) loads column m % 8 of its group; the lanes of a row
+          // (equal kg) then read column u's from lane u
+          const int k = (s * 4 + kg) * 8 + (m & 7);
+          return (int32_t)__builtin_amdgcn_raw_buffer_load_b32(rc, (uint32_t)k * 4, 0, 0);
         };
-        v8u ah, al;
-        int32_t xr[8];
-        if (K > 0) fetch(0, ah, al, xr);
-        for (int s = 0; s < nsteps; ++s) {
-          float xv[NT][8];
+        auto ld_val = [&](int s, v8u &h, v8u &l) {
+          const uint32_t off = vlane + (uint32_t)(s * 32 * b) * sizeof(uint16_t);
+          h = __builtin_bit_cast(v8u, __builtin_amdgcn_raw_buffer_load_b128(rh, off, 0, 2));
+          l = __builtin_bit_cast(v8u, __builtin_amdgcn_raw_buffer_load_b128(rl, off, 0, 2));
+        };
+        auto ld_x = [&](int s, int32_t xg, float(&xv)[NT][8]) {
+          const int k0 = (s * 4 + kg) * 8;
+          const int32_t xo =
+              XB ? (k0 + (m & 7) < K
+                        ? (int32_t)(uint32_t)((int64_t)xg * P.ldx * (int64_t)sizeof(float))
+                        : (int32_t)kOut)
+                 : xg;
+          const int32_t xi[8] = {row_bcast<0>(xo), row_bcast<1>(xo), row_bcast<2>(xo),
+                                 row_bcast<3>(xo), row_bcast<4>(xo), row_bcast<5>(xo),
+                                 row_bcast<6>(xo), row_bcast<7>(xo)};
 #pragma unroll
-          for (int u = 0; u < 8; ++u) {
-            const bool kin = (s * 4 + kg) * 8 + u < K;
-            const float *xp = P.X + (int64_t)xr[u] * P.ldx;
+          for (int u = 0; u < 8; ++u)
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
-              const float v = xp[nn[t]];
-              xv[t][u] = (kin && nok[t]) ? v : 0.0f;
+              if constexpr (XB) {
+                // padding columns read zeros; four neighbouring lanes are in
+                // range together (as in the FP32 kernel)
+                xv[t][u] = buf_load<float>(rx, c0 + t * 16 + (m & ~3) < P.nrhs
+                                                   ? (uint32_t)xi[u] + xcol + t * 64u
+                                                   : kOut);
+              } else {
+                const int n = c0 + t * 16 + m;
+                const float *xp = k0 + u < K && n < P.nrhs ? P.X + (int64_t)xi[u] * P.ldx + n
+                                                           : zero_row<float>();
+                xv[t][u] = *xp;
+              }
             }
-          }
-          v8u nh, nl;
-          int32_t xn[8];
-          fetch(min(s + 1, nsteps - 1), nh, nl, xn);
+        };
+        auto mma = [&](const v8u &ah, const v8u &al, const float(&xv)[NT][8]) {
 #pragma unroll
           for (int t = 0; t < NT; ++t) {
             v8u xh, xl;
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-              const unsigned short h = bf16_rne(xv[t][u]);
-              xh[u] = h;
-              xl[u] = bf16_rne(xv[t][u] - bf16_to_f32(h));
-            }
+            split_bf16(xv[t], xh, xl);
             acc[t] = mfma_bf16(ah, xh, acc[t]);
             acc[t] = mfma_bf16(ah, xl, acc[t]);
             acc[t] = mfma_bf16(al, xh, acc[t]);
           }
-          ah = nh;
-          al = nl;
+        };
+        v8u vh[2], vl[2];
+        float xv[2][NT][8];
+        int32_t xi[2] = {ld_idx(0), ld_idx(1)};
+        ld_x(0, xi[0], xv[0]);
+        ld_val(0, vh[0], vl[0]);
+        xi[0] = ld_idx(2);
+        __builtin_amdgcn_sched_barrier(0);
+        int s = 0;
+        for (; s + 2 <= nsteps; s += 2) {
 #pragma unroll
-          for (int u = 0; u < 8; ++u) xr[u] = xn[u];
+          for (int r = 0; r < 2; ++r) {
+            const int q = r ^ 1;
+            ld_x(s + r + 1, xi[q], xv[q]);
+            ld_val(s + r + 1, vh[q], vl[q]);
+            xi[q] = ld_idx(s + r + 3);
+            __builtin_amdgcn_sched_barrier(0);
+            mma(vh[r], vl[r], xv[r]);
+            __builtin_amdgcn_sched_barrier(0);
+          }
         }
+        if (s < nsteps) mma(vh[0], vl[0], xv[0]);
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
           const int n = c0 + t * 16 + m;
@@ -875,18 +956,14 @@ __global__ void __launch_bounds__(kThreads) k_spmm_bf16x3(FwdParams<float> P) {
 
 // BF16x3 fast path: 64 right-hand sides per pass, tile t of lane m holds
 // column c0 + 4m + t, so the 8 X rows of a lane's 8-column group arrive as
-// eight 16-byte loads; each row splits into hi/lo with the hardware
-// round-to-nearest-even conversion (two values per instruction).  The loop
-// is branch-free and double-buffered like the FP64/FP32 matrix-core kernel.
-typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ unsigned int pack_bf16(float a, float b) {
-  return __builtin_bit_cast(unsigned int, v2bf{(__bf16)a, (__bf16)b});
-}
+// eight 16-byte loads.  With one index register a lane, broadcast along the
+// row, instead of two 16-byte index loads that were compared with the panel's
+// end at once (and so waited for): Chebyshev step on the 32^3 lattice b = 13,
+// nrhs 64: 240 -> 199 us (184 -> 158 registers).
 
 template <bool MOM, bool XB>
 __global__ void __launch_bounds__(kThreads) k_spmm_bf16x3_vx(FwdParams<float> P) {
   extern __shared__ double s_mom[];
-  typedef unsigned int v4u __attribute__((ext_vector_type(4)));
   const int wg = xcd_remap(blockIdx.x, gridDim.x);
   const int w = wave_id();
   const int lane = threadIdx.x & 63;
@@ -922,32 +999,36 @@ __global__ void __launch_bounds__(kThreads) k_spmm_bf16x3_vx(FwdParams<float> P)
         // the 8 columns 32 s + 8 kg + u.  Two register sets alternate as in
         // the FP64/FP32 kernel: indices run two steps ahead, values and X
         // rows one step ahead.
-        auto ld_idx = [&](int s, int32_t(&xi)[8]) {
-          // the 8 column indices of the lane's group: two 16-byte loads
-          // (past the panel's table the buffer reads zero; masked by k < K)
-          const int k0 = (s * 4 + kg) * 8;
-#pragma unroll
-          for (int h = 0; h < 2; ++h) {
-            const v4u32 q = __builtin_bit_cast(
-                v4u32, __builtin_amdgcn_raw_buffer_load_b128(rc, (uint32_t)(k0 + 4 * h) * 4, 0, 0));
-#pragma unroll
-            for (int u = 0; u < 4; ++u) xi[4 * h + u] = k0 + 4 * h + u < K ? (int32_t)q[u] : -1;
-          }
+        auto ld_idx = [&](int s) {
+          // lane (m, kg) loads column m % 8 of its group; the lanes of a row
+          // (equal kg) then read column u's from lane u
+          const int k = (s * 4 + kg) * 8 + (m & 7);
+          return (int32_t)__builtin_amdgcn_raw_buffer_load_b32(rc, (uint32_t)k * 4, 0, 0);
         };
         auto ld_val = [&](int s, v8u &h, v8u &l) {
           const uint32_t off = vlane + (uint32_t)(s * 32 * b) * sizeof(uint16_t);
           h = __builtin_bit_cast(v8u, __builtin_amdgcn_raw_buffer_load_b128(rh, off, 0, 2));
           l = __builtin_bit_cast(v8u, __builtin_amdgcn_raw_buffer_load_b128(rl, off, 0, 2));
         };
-        auto ld_x = [&](const int32_t(&xi)[8], float4(&xv)[8]) {
+        auto ld_x = [&](int s, int32_t xg, float4(&xv)[8]) {
+          const int k0 = (s * 4 + kg) * 8;
+          // XB: byte offset of the lane's own column, past the descriptor for
+          // a padding column (reads zeros)
+          const int32_t xo =
+              XB ? (k0 + (m & 7) < K
+                        ? (int32_t)(uint32_t)((int64_t)xg * P.ldx * (int64_t)sizeof(float))
+                        : (int32_t)kOut)
+                 : xg;
+          const int32_t xi[8] = {row_bcast<0>(xo), row_bcast<1>(xo), row_bcast<2>(xo),
+                                 row_bcast<3>(xo), row_bcast<4>(xo), row_bcast<5>(xo),
+                                 row_bcast<6>(xo), row_bcast<7>(xo)};
 #pragma unroll
           for (int u = 0; u < 8; ++u) {
             if constexpr (XB) {
-              const uint32_t ro =
-                  xi[u] >= 0 ? (uint32_t)((int64_t)xi[u] * P.ldx * (int64_t)sizeof(float)) + xcol : kOut;
-              xv[u] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rx, ro, 0, 0));
+              xv[u] = __builtin_bit_cast(
+                  float4, __builtin_amdgcn_raw_buffer_load_b128(rx, (uint32_t)xi[u] + xcol, 0, 0));
             } else {
-              const float *xp = xi[u] >= 0 ? P.X + (int64_t)xi[u] * P.ldx + c0 : zero_row<float>();
+              const float *xp = k0 + u < K ? P.X + (int64_t)xi[u] * P.ldx + c0 : zero_row<float>();
               xv[u] = *reinterpret_cast<const float4 *>(xp + 4 * m);
             }
           }
@@ -955,43 +1036,37 @@ __global__ void __launch_bounds__(kThreads) k_spmm_bf16x3_vx(FwdParams<float> P)
         auto mma = [&](const v8u &ah, const v8u &al, const float4(&xv)[8]) {
 #pragma unroll
           for (int t = 0; t < 4; ++t) {
-            v4u hi, lo;
+            float x[8];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              const float x0 = reinterpret_cast<const float *>(&xv[2 * q])[t];
-              const float x1 = reinterpret_cast<const float *>(&xv[2 * q + 1])[t];
-              const unsigned int h = pack_bf16(x0, x1);
-              hi[q] = h;
-              lo[q] = pack_bf16(x0 - __uint_as_float(h << 16), x1 - __uint_as_float(h & 0xFFFF0000u));
-            }
-            const v8u xh = __builtin_bit_cast(v8u, hi), xl = __builtin_bit_cast(v8u, lo);
+            for (int u = 0; u < 8; ++u) x[u] = reinterpret_cast<const float *>(&xv[u])[t];
+            v8u xh, xl;
+            split_bf16(x, xh, xl);
             acc[t] = mfma_bf16(ah, xh, acc[t]);
             acc[t] = mfma_bf16(ah, xl, acc[t]);
             acc[t] = mfma_bf16(al, xh, acc[t]);
           }
         };
-        v8u hA, lA, hB, lB;
-        float4 xA[8], xB[8];
-        int32_t iA[8], iB[8];
-        ld_idx(0, iA);
-        ld_idx(1, iB);
-        ld_x(iA, xA);
-        ld_val(0, hA, lA);
-        for (int s = 0; s < nsteps; s += 2) {
-          ld_idx(s + 2, iA);
-          ld_x(iB, xB);
-          ld_val(s + 1, hB, lB);
-          __builtin_amdgcn_sched_barrier(0);
-          mma(hA, lA, xA);
-          __builtin_amdgcn_sched_barrier(0);
-          if (s + 1 >= nsteps) break;
-          ld_idx(s + 3, iB);
-          ld_x(iA, xA);
-          ld_val(s + 2, hA, lA);
-          __builtin_amdgcn_sched_barrier(0);
-          mma(hB, lB, xB);
-          __builtin_amdgcn_sched_barrier(0);
+        v8u vh[2], vl[2];
+        float4 xv[2][8];
+        int32_t xi[2] = {ld_idx(0), ld_idx(1)};
+        ld_x(0, xi[0], xv[0]);
+        ld_val(0, vh[0], vl[0]);
+        xi[0] = ld_idx(2);
+        __builtin_amdgcn_sched_barrier(0);
+        int s = 0;
+        for (; s + 2 <= nsteps; s += 2) {
+#pragma unroll
+          for (int r = 0; r < 2; ++r) {
+            const int q = r ^ 1;
+            ld_x(s + r + 1, xi[q], xv[q]);
+            ld_val(s + r + 1, vh[q], vl[q]);
+            xi[q] = ld_idx(s + r + 3);
+            __builtin_amdgcn_sched_barrier(0);
+            mma(vh[r], vl[r], xv[r]);
+            __builtin_amdgcn_sched_barrier(0);
+          }
         }
+        if (s < nsteps) mma(vh[0], vl[0], xv[0]);
         double mmv[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -1923,10 +1998,19 @@ bool vectorizable(const FwdParams<T> &p, int nt) {
 
 template <int NT>
 hipError_t launch_bf16_nt(const FwdParams<float> &p, hipStream_t s, dim3 grid, size_t shm) {
-  if (p.mom)
-    hipLaunchKernelGGL((k_spmm_bf16x3<NT, true>), grid, dim3(kThreads), shm, s, p);
-  else
-    hipLaunchKernelGGL((k_spmm_bf16x3<NT, false>), grid, dim3(kThreads), 0, s, p);
+  // one buffer descriptor covers X when its rows span less than 2^31 bytes
+  const bool xb = p.xrows * p.ldx * (int64_t)sizeof(float) < (int64_t(1) << 31);
+  if (p.mom) {
+    if (xb)
+      hipLaunchKernelGGL((k_spmm_bf16x3<NT, true, true>), grid, dim3(kThreads), shm, s, p);
+    else
+      hipLaunchKernelGGL((k_spmm_bf16x3<NT, true, false>), grid, dim3(kThreads), shm, s, p);
+  } else {
+    if (xb)
+      hipLaunchKernelGGL((k_spmm_bf16x3<NT, false, true>), grid, dim3(kThreads), 0, s, p);
+    else
+      hipLaunchKernelGGL((k_spmm_bf16x3<NT, false, false>), grid, dim3(kThreads), 0, s, p);
+  }
   return hipGetLastError();
 }
 

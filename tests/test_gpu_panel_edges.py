@@ -58,3 +58,24 @@ def test_product_at_every_width(op, prec, nrhs):
     got = host(A.spmm_t(dev(X, prec)))
     check(got, ref, prec, oracle.abs_product(op, X, transpose_op=True), "adjoint %s %d" % (prec, nrhs))
     assert not got[0].any()
+
+
+@pytest.mark.parametrize("prec,nrhs", [("fp64", 3), ("fp64", 6), ("fp64", 13), ("fp32", 5), ("fp32", 9),
+                                       ("fp32", 13), ("fp32", 22), ("fp32", 50), ("bf16x3", 1),
+                                       ("bf16x3", 13), ("bf16x3", 50)])
+def test_columns_beside_the_vectors_do_not_matter(op, prec, nrhs):
+    """X and Y are column slices of wider arrays: what lies beside X (NaN) is
+    read at most into columns that are not stored, what lies beside Y stays."""
+    print("case slices", prec, nrhs, flush=True)
+    A = Matrix.from_operator(op, prec=prec)
+    X = rounded(np.random.default_rng(nrhs).standard_normal((op.N, nrhs)), prec)
+    ref = oracle.spmm(op, X)
+    for lead, tail in ((3, 2), (4, 0), (0, 7)):
+        wide = np.full((op.N, lead + nrhs + tail), np.nan)
+        wide[:, lead:lead + nrhs] = X
+        Xd = dev(wide, prec)[:, lead:lead + nrhs]
+        Yw = dev(np.full_like(wide, 7.0), prec)
+        A.spmm(Xd, Yw[:, lead:lead + nrhs])
+        got = host(Yw)
+        check(got[:, lead:lead + nrhs], ref, prec, oracle.abs_product(op, X), "slice %d" % lead)
+        assert (got[:, :lead] == 7.0).all() and (got[:, lead + nrhs:] == 7.0).all()
