@@ -247,6 +247,7 @@ struct DevDir {
   int64_t *colg = nullptr;    // forward direction only
   int64_t n_values = 0, n_values16 = 0;
   int32_t npanels = 0;        // forward: block rows; transposed: block columns
+  double pad16 = 1.0;         // panel rows in tiles of 16 over those in tiles of 4
 };
 
 int env_path() {
@@ -369,16 +370,49 @@ int require_square(const vbcsr_mat *A, const char *where) {
   return VBCSR_OK;
 }
 
+// Rows that 16-row tiles take for panels of these heights over those that
+// 4-row tiles take (1 to 4): what the small tiles save.
+template <typename It>
+double pad_ratio(It first, It last) {
+  int64_t r16 = 0, r4 = 0;
+  for (; first != last; ++first) {
+    const int64_t b = *first;
+    r16 += (b + 15) / 16 * 16;
+    r4 += (b + 3) / 4 * 4;
+  }
+  return r4 ? (double)r16 / (double)r4 : 1.0;
+}
+
 struct Route {
   Kind kind;
   int tile;
 };
 
-Route route(const vbcsr_mat *A, int32_t nrhs) {
+Route route(const vbcsr_mat *A, int d, int32_t nrhs) {
   int path = env_path();
   if (path == VBCSR_PATH_AUTO) path = A->opts.path;
   if (A->prec == VBCSR_BF16X3) return {Kind::Bf16x3, nrhs <= 16 ? 1 : nrhs <= 32 ? 2 : 4};
-  bool vec = path == VBCSR_PATH_VEC || (path == VBCSR_PATH_AUTO && nrhs <= 8);
+  // FP64 small tiles where the path is left open: 3 to 8 right-hand sides on
+  // any operator (from level, b = 13 at 4, to 34 % faster, b = 1/4/9 at 8); 9
+  // to 16 unless 16-row tiles pad nothing (b = 13: 217 us against 227 at 16;
+  // b = 13/9/1, ratio 1.14: 276 against 263 at 12; b = 9..20, ratio 1.33: 177
+  // against 141 at 16); 17 to 32 where they pad more (b = 13/9/1 309 against
+  // 318 at 20; b = 9..20 240 against 218 at 32; b = 1/4/9 197 against 178 at
+  // 24); 2 where they pad to twice the rows (b = 8: 112 against 105 us, b =
+  // 1/4/9 98 against 89; b = 9..20 98 against 104, b = 13/9/1 179 against
+  // 200); 1 nowhere.
+  if (A->prec == VBCSR_FP64 && path == VBCSR_PATH_AUTO && A->opts.nrhs_tile == 0) {
+    const double pad = A->dir[d].pad16;
+    if ((nrhs >= 3 && nrhs <= 8) || (nrhs >= 9 && nrhs <= 16 && pad > 1.05) ||
+        (nrhs >= 17 && nrhs <= 32 && pad > 1.25) || (nrhs == 2 && pad > 1.75))
+      return {Kind::Small, 0};
+  }
+  // FP32: 5 to 8 right-hand sides are faster on 16-wide tiles than in the
+  // vector kernel's passes of 8 (particle 6: 157 against 138 us, 100,000
+  // atoms of b = 1/4/9 6: 198 against 139, 8: 173 against 141; lattice 8: 118
+  // against 109), up to 4 are not (particle 4: 121 against 131)
+  const int32_t vec_max = A->prec == VBCSR_FP32 && A->opts.nrhs_tile == 0 ? 4 : 8;
+  bool vec = path == VBCSR_PATH_VEC || (path == VBCSR_PATH_AUTO && nrhs <= vec_max);
   if (vec) {
     int t = A->opts.nrhs_tile;
     if (t != 1 && t != 2 && t != 4 && t != 8) t = nrhs <= 1 ? 1 : nrhs <= 2 ? 2 : nrhs <= 4 ? 4 : 8;
@@ -394,7 +428,7 @@ int product(const vbcsr_mat *A, int d, const void *X, int64_t ldx, const void *Y
   if (d == 1 && A->tr_stale)
     return fail(VBCSR_EINVAL, "the transposed pages are stale: call vbcsr_refresh_transposed");
   const DevDir &D = A->dir[d];
-  const Route rt = route(A, nrhs);
+  const Route rt = route(A, d, nrhs);
   hipError_t e;
   if (A->prec == VBCSR_FP64) {
     FwdParams<double> p{};
@@ -561,6 +595,7 @@ int create_impl(vbcsr_mat **out, int32_t n_atoms, const int32_t *block_sizes,
     D.n_values = P.n_values;
     D.n_values16 = P.n_values16;
     D.npanels = (int32_t)P.rows.size();
+    D.pad16 = pad_ratio(block_sizes, block_sizes + P.rows.size());
     if ((rc = upload_into(A, &D.rows, P.rows, s))) return bail(rc);
     if ((rc = upload_into(A, &D.blk_pos, P.blk_pos, s))) return bail(rc);
     if ((rc = upload_into(A, &D.blk_k0, P.blk_k0, s))) return bail(rc);
@@ -674,6 +709,7 @@ int create_planned_on_device(vbcsr_mat **out, const vbcsr_mat *A, int64_t nnzb, 
     D.n_values = po.dir[d].n_values;
     D.n_values16 = 0;
     D.npanels = n;
+    D.pad16 = A->dir[d].pad16;
     if ((rc = finish_direction(C, d, po.dir[d].n_cols, s))) return rc;
   }
   if (C->nnz > 0 && d_vals && (rc = pack_all(C, d_vals, 0, s))) return rc;

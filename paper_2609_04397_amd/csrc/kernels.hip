@@ -154,7 +154,14 @@ template <> __device__ __forceinline__ float buf_load<float>(__amdgpu_buffer_rsr
   return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
 }
 
-// Bytes from X's first element to its last (XB kernels: below 2^31).
+// One buffer descriptor serves X when its rows span less than kXSpan bytes.
+// Byte offsets are then the sum of a row part (kOutRow for a padding column)
+// and a column part (kOutCol for a lane past nrhs): a sum with either or both
+// lies beyond every such span and below 2^32, so the load returns zero.
+constexpr int64_t kXSpan = (int64_t(1) << 31) - 4096;
+constexpr uint32_t kOutRow = 0x80000000u, kOutCol = 0x7FFFF000u;
+
+// Bytes from X's first element to its last (XB kernels: below kXSpan).
 template <typename T> __device__ __forceinline__ uint32_t x_span(const FwdParams<T> &P) {
   return P.xrows > 0
              ? (uint32_t)(((P.xrows - 1) * P.ldx + P.nrhs) * (int64_t)sizeof(T))
@@ -534,6 +541,225 @@ __global__ void __launch_bounds__(kThreads) k_spmm_vp(FwdParams<T> P) {
 }
 
 // ---------------------------------------------------------------------------
+// FP64 product on small matrix-core tiles, few right-hand sides
+// ---------------------------------------------------------------------------
+// The four 4x4 blocks of v_mfma_f64_4x4x4 (which runs at the rate of the
+// 16x16x4 one: 75 of 78 TFLOP/s measured) take 4 panel rows x 4 panel columns
+// each against the X rows of those columns and 4 right-hand sides: a step is
+// 16 panel columns, the blocks' partial sums meet once per panel.  Rows pad
+// to 4 and right-hand sides to 4 or 8 instead of 16.  Lane 16 k + 4 q + i
+// works on column 4 k + q of the step and on row i of a row group (values) or
+// on right-hand sides LW i .. LW i + LW - 1 of every 4 LW (X).
+//
+// Bound by the load path like the kernel below, so both operands come 16
+// bytes a lane, straight into the operand registers: two rows of a column
+// (row groups g = 0, 1 are its even and odd rows; 5 to 8 rows one load, 9 to
+// 12 one of 16 and one of 8 bytes, 13 to 16 two) and two right-hand sides of
+// an X row, 16 rows a load.  The vector kernel needs 8-byte value loads and a
+// round trip through LDS per chunk, the 16x16 tiles waste half their columns
+// on 8 right-hand sides and take 4 + 4 loads per 16 columns where these take
+// 2 + 2.  A ring of R register sets as in the kernel below.  Values are read
+// through the caches: two loads share each line (streamed past them, nrhs 16
+// on b = 9..20 took 203 us instead of 162).  Up to 32 rows go in one pass (162
+// -> 141).  Before (vector kernel up to 8 right-hand sides, 16x16 tiles
+// beyond) and now, us: 40,000-atom particle nrhs 8 259 -> 234, nrhs 6 270 ->
+// 227, nrhs 12 276 -> 263; b = 13 lattice nrhs 8 217 -> 195; 50,000 atoms of
+// b = 1/4/9 nrhs 4 131 -> 88, nrhs 8 148 -> 98, nrhs 16 154 -> 127, nrhs 32
+// 204 -> 197; b = 9..20 nrhs 8 140 -> 123, nrhs 16 200 -> 141, nrhs 32 246 ->
+// 217.
+template <typename T, int RG, int NG, int LW, bool MOM, int R>
+__device__ __forceinline__ void small_rows(const FwdParams<T> &P, const RowDesc &rd, int m0, int c0,
+                                           double *s_mom) {
+  static_assert(sizeof(T) == 8, "FP64 tiles");
+  constexpr int NL = NG / LW;            // X loads per step
+  constexpr int NV = (RG + 1) / 2;       // value loads per step
+  const int lane = threadIdx.x & 63;
+  const int ij = lane & 3;
+  const int col = 4 * (lane >> 4) + ((lane >> 2) & 3);
+  const int b = rd.b, K = rd.K;
+  const __amdgpu_buffer_rsrc_t rv =
+      panel_rsrc(P.vals + rd.vbase, (uint32_t)((int64_t)K * b * sizeof(T)));
+  const __amdgpu_buffer_rsrc_t rc = panel_rsrc(P.colx + rd.cbase, (uint32_t)(K * 4));
+  const __amdgpu_buffer_rsrc_t rx = panel_rsrc(P.X, x_span(P));
+  double acc[RG][NG];
+#pragma unroll
+  for (int g = 0; g < RG; ++g)
+#pragma unroll
+    for (int t = 0; t < NG; ++t) acc[g][t] = 0.0;
+  // load v covers row groups 2v and 2v + 1, or with RG odd the last one alone
+  auto single = [](int v) { return 2 * v + 1 == RG; };
+  uint32_t vo[NV];
+#pragma unroll
+  for (int v = 0; v < NV; ++v)
+    vo[v] = (uint32_t)(col * b + m0 + 8 * v + (single(v) ? ij : 2 * ij)) * 8u;
+  const uint32_t vstep = (uint32_t)(16 * b) * 8u;
+  uint32_t xcol[NL];
+#pragma unroll
+  for (int l = 0; l < NL; ++l) {
+    const int c = c0 + 4 * LW * l + LW * ij;
+    xcol[l] = c < P.nrhs ? (uint32_t)c * 8u : kOutCol;
+  }
+  auto ld_idx = [&](int s) {
+    return (int32_t)__builtin_amdgcn_raw_buffer_load_b32(rc, (uint32_t)(16 * s + col) * 4, 0, 0);
+  };
+  auto ld_val = [&](int s, double (&av)[RG]) {
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      const uint32_t off = vo[v] + (uint32_t)s * vstep;
+      if (single(v)) {
+        av[2 * v] = buf_load<double>(rv, off);
+      } else {
+        const double2 q =
+            __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(rv, off, 0, 0));
+        av[2 * v] = q.x;
+        av[(2 * v + 1) % RG] = q.y;
+      }
+    }
+  };
+  auto ld_x = [&](int s, int32_t xi, double (&xv)[NG]) {
+    const uint32_t ro =
+        16 * s + col < K ? (uint32_t)((int64_t)xi * P.ldx * (int64_t)sizeof(T)) : kOutRow;
+#pragma unroll
+    for (int l = 0; l < NL; ++l) {
+      if constexpr (LW == 2) {
+        const double2 q =
+            __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(rx, ro + xcol[l], 0, 0));
+        xv[2 * l] = q.x;
+        xv[2 * l + 1] = q.y;
+      } else {
+        xv[l] = buf_load<double>(rx, ro + xcol[l]);
+      }
+    }
+  };
+  auto mma = [&](const double (&av)[RG], const double (&xv)[NG]) {
+#pragma unroll
+    for (int g = 0; g < RG; ++g)
+#pragma unroll
+      for (int t = 0; t < NG; ++t)
+        acc[g][t] = __builtin_amdgcn_mfma_f64_4x4x4f64(av[g], xv[t], acc[g][t], 0, 0, 0);
+  };
+  const int ns = (K + 15) >> 4;
+  double av[R][RG], xv[R][NG];
+  int32_t xi[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) xi[r] = ld_idx(r);
+#pragma unroll
+  for (int r = 0; r + 1 < R; ++r) {
+    ld_x(r, xi[r], xv[r]);
+    ld_val(r, av[r]);
+    xi[r] = ld_idx(r + R);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  int s = 0;
+  for (; s + R <= ns; s += R) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int q = (r + R - 1) % R;
+      ld_x(s + r + R - 1, xi[q], xv[q]);
+      ld_val(s + r + R - 1, av[q]);
+      xi[q] = ld_idx(s + r + 2 * R - 1);
+      __builtin_amdgcn_sched_barrier(0);
+      mma(av[r], xv[r]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+#pragma unroll
+  for (int r = 0; r + 1 < R; ++r)
+    if (s + r < ns) mma(av[r], xv[r]);
+  // sum over the four blocks; then, four row groups at a time, lane
+  // 16 i + 4 g + j writes the row that row group g holds at i, right-hand
+  // sides j of each tile
+  const int gl = (lane >> 2) & 3, il = lane >> 4;
+  double mm[NG];
+#pragma unroll
+  for (int t = 0; t < NG; ++t) mm[t] = 0.0;
+#pragma unroll
+  for (int h = 0; h < RG; h += 4) {
+    double y[NG];
+#pragma unroll
+    for (int t = 0; t < NG; ++t) y[t] = 0.0;
+#pragma unroll
+    for (int g = h; g < h + 4 && g < RG; ++g)
+#pragma unroll
+      for (int t = 0; t < NG; ++t) {
+        double a = acc[g][t];
+        a += __shfl_xor(a, 4, 64);
+        a += __shfl_xor(a, 8, 64);
+        y[t] = gl == g - h ? a : y[t];
+      }
+    const int gr = h + gl;   // this lane's row group
+    const int prow = 8 * (gr >> 1) + (single(gr >> 1) ? il : 2 * il + (gr & 1));
+    const bool ok = gr < RG && m0 + prow < b;
+    const int64_t r = (int64_t)rd.yrow + m0 + prow;
+#pragma unroll
+    for (int l = 0; l < NL; ++l) {
+      const int cc = c0 + 4 * LW * l + LW * ij;
+      if (ok && LW == 2 && P.yrow16 && cc + 2 <= P.nrhs) {
+        double2 v = {P.alpha * y[LW * l], P.alpha * y[LW * l + LW - 1]};
+        if (P.beta != 0.0) {
+          const double2 q = *reinterpret_cast<const double2 *>(P.Yin + r * P.ldyin + cc);
+          v.x = fma(P.beta, q.x, v.x);
+          v.y = fma(P.beta, q.y, v.y);
+        }
+        *reinterpret_cast<double2 *>(P.Yout + r * P.ldy + cc) = v;
+        if (MOM) {
+          const double2 q = *reinterpret_cast<const double2 *>(P.R + r * P.ldr + cc);
+          mm[LW * l] += q.x * v.x;
+          mm[LW * l + LW - 1] += q.y * v.y;
+        }
+      } else if (ok) {
+#pragma unroll
+        for (int e = 0; e < LW; ++e) {
+          if (cc + e < P.nrhs) {
+            double v = P.alpha * y[LW * l + e];
+            if (P.beta != 0.0) v = fma(P.beta, P.Yin[r * P.ldyin + cc + e], v);
+            P.Yout[r * P.ldy + cc + e] = v;
+            if (MOM) mm[LW * l + e] += P.R[r * P.ldr + cc + e] * v;
+          }
+        }
+      }
+    }
+  }
+  if (MOM) {
+#pragma unroll
+    for (int t = 0; t < NG; ++t) {
+      double v = mm[t];
+#pragma unroll
+      for (int o = 4; o <= 32; o <<= 1) v += __shfl_xor(v, o, 64);
+      const int n = c0 + 4 * LW * (t / LW) + LW * ij + t % LW;
+      if (lane < 4 && n < P.nrhs) s_mom[wave_id() * P.nrhs + n] += v;
+    }
+  }
+}
+
+// NG groups of 4 right-hand sides per pass; LW right-hand sides per X load.
+template <int NG, int LW, bool MOM, int R>
+__global__ void __launch_bounds__(kThreads) k_spmm_small(FwdParams<double> P) {
+  extern __shared__ double s_mom[];
+  constexpr int MR = NG <= 4 ? 32 : 16;   // panel rows per pass
+  const int wg = xcd_remap(blockIdx.x, gridDim.x);
+  const int row = wg * kWaves + wave_id();
+  mom_init<MOM>(s_mom, P.nrhs);
+  if (row < P.nrows) {
+    const RowDesc rd = P.rows[row];
+    for (int c0 = 0; c0 < P.nrhs; c0 += 4 * NG)
+      for (int m0 = 0; m0 < rd.b; m0 += MR) {
+        // 29 to 32 rows and 25 to 28 share a case; those past MR are not reached
+        switch ((min(rd.b - m0, MR) + 3) >> 2) {
+          case 1: small_rows<double, 1, NG, LW, MOM, R>(P, rd, m0, c0, s_mom); break;
+          case 2: small_rows<double, 2, NG, LW, MOM, R>(P, rd, m0, c0, s_mom); break;
+          case 3: small_rows<double, 3, NG, LW, MOM, R>(P, rd, m0, c0, s_mom); break;
+          case 4: small_rows<double, 4, NG, LW, MOM, R>(P, rd, m0, c0, s_mom); break;
+          case 5: small_rows<double, MR >= 20 ? 5 : 4, NG, LW, MOM, R>(P, rd, m0, c0, s_mom); break;
+          case 6: small_rows<double, MR >= 24 ? 6 : 4, NG, LW, MOM, R>(P, rd, m0, c0, s_mom); break;
+          default: small_rows<double, MR >= 32 ? 8 : 4, NG, LW, MOM, R>(P, rd, m0, c0, s_mom); break;
+        }
+      }
+  }
+  mom_flush<MOM>(s_mom, P.nrhs, wg, P.mom);
+}
+
+// ---------------------------------------------------------------------------
 // FP64 / FP32 matrix-core product
 // ---------------------------------------------------------------------------
 // A operand: the panel's 4-column slice (contiguous, 4*b values, panel row m
@@ -567,16 +793,39 @@ __global__ void __launch_bounds__(kThreads) k_spmm_vp(FwdParams<T> P) {
 // gain 2 % on the lattice and lose 4 % on the small blocks, groups of one
 // slice lose on the lattice.
 //
-// Fast path (VX = true): the N index of the 16x16 tiles is permuted so that
-// lane m of tile t holds right-hand side c0 + l*16*VEC + VEC*m + e, with
-// t = l*VEC + e and VEC elements per 16 bytes: one 16-byte load per lane and
-// X row fetches VEC tiles, and outputs are written back 16 bytes at a time.
-// It needs 16-byte aligned vectors, leading dimensions that are multiples of
-// VEC and nrhs a multiple of 16*VEC*L.  The generic path (VX = false) loads
-// one element per lane and tile and handles any nrhs and leading dimension.
+// VX: the N index of the 16x16 tiles is permuted so that lane m of tile t
+// holds right-hand side c0 + l*16*VEC + VEC*m + e, with t = l*VEC + e and VEC
+// elements per 16 bytes: one 16-byte load per lane and X row fetches VEC
+// tiles, and outputs leave 16 bytes at a time where the vectors' alignment
+// allows (yrow16).  A buffer load needs no more than 4-byte alignment, so with
+// XB this serves every nrhs and leading dimension that fill VEC tiles (a
+// lane's elements past nrhs go to columns that are not stored); with one
+// 8-byte load per tile FP64 nrhs 20 and 50 took 367 and 600 us on the
+// 40,000-atom particle, now 309 and 497.
+// Without XB it needs 16-byte aligned rows and whole passes.  The other
+// form (VX = false) loads one element per lane and tile.
 template <typename T> struct Vec16;
 template <> struct Vec16<double> { using type = double2; static constexpr int n = 2; };
 template <> struct Vec16<float> { using type = float4; static constexpr int n = 4; };
+
+// Lane m < 8 of a 16-lane row holds rows 2m (x) and 2m + 1 (y) of one panel
+// column, lane m >= 8 rows 2 (m - 8) and 2 (m - 8) + 1 of the next: a gets
+// the first column, even rows in lanes 0-7 and odd rows in lanes 8-15, b the
+// second (two data-parallel moves per half, no memory).
+__device__ __forceinline__ int tile_row(int m) { return m < 8 ? 2 * m : 2 * m - 15; }
+template <typename T> __device__ __forceinline__ void fill_pair(T x, T y, T &a, T &b) {
+  static_assert(sizeof(T) == 8, "two 32-bit halves");
+  const v2u32 xi = __builtin_bit_cast(v2u32, x), yi = __builtin_bit_cast(v2u32, y);
+  v2u32 ai, bi;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    // 0x128: row_ror:8; bank masks 0xC / 0x3: lanes 8-15 / 0-7 of each row
+    ai[h] = (uint32_t)__builtin_amdgcn_update_dpp((int)xi[h], (int)yi[h], 0x128, 0xF, 0xC, false);
+    bi[h] = (uint32_t)__builtin_amdgcn_update_dpp((int)yi[h], (int)xi[h], 0x128, 0xF, 0x3, false);
+  }
+  a = __builtin_bit_cast(T, ai);
+  b = __builtin_bit_cast(T, bi);
+}
 
 template <typename T, int NT, bool MOM, bool VX, bool XB>
 __global__ void __launch_bounds__(kThreads) k_spmm_mfma(FwdParams<T> P) {
@@ -586,6 +835,7 @@ __global__ void __launch_bounds__(kThreads) k_spmm_mfma(FwdParams<T> P) {
   constexpr int VEC = Vec16<T>::n;
   constexpr int NL = VX ? NT / VEC : 0;  // 16-byte loads per lane and X row
   constexpr int U = 2;                    // slices per group
+  constexpr bool PAIR = sizeof(T) == 8;   // values two rows at a time
   constexpr int R = NT * sizeof(T) <= 8 ? 4 : 3;  // groups in the ring
   static_assert(!VX || NT % VEC == 0, "tile count must fill whole 16-byte loads");
   const int wg = xcd_remap(blockIdx.x, gridDim.x);
@@ -611,61 +861,85 @@ __global__ void __launch_bounds__(kThreads) k_spmm_mfma(FwdParams<T> P) {
         V acc[NT];
 #pragma unroll
         for (int t = 0; t < NT; ++t) acc[t] = V{};
-        // panel sizes are below 2^31 bytes (checked at creation), so kOut is
-        // past the end of every panel and reads zero
-        constexpr uint32_t kOut = 0x80000000u;
         const __amdgpu_buffer_rsrc_t rv = panel_rsrc(vals, (uint32_t)((int64_t)K * b * sizeof(T)));
         const __amdgpu_buffer_rsrc_t rc = panel_rsrc(cx, (uint32_t)(K * 4));
-        // Rows past the panel: 4-byte loads read the next column's values
-        // into tile rows that are never stored, since four neighbouring lanes
-        // of which some are out of range take the slow path of the load unit
-        // (16 cycles instead of 4.7; FP32 nrhs 32 on the small blocks 285 ->
-        // 240 us); 8-byte loads cost 16 cycles anyway and stay masked.
-        const uint32_t vlane =
-            sizeof(T) == 4 || p < b ? (uint32_t)(kq * b + p) * sizeof(T) : kOut;
+        // FP32: lane (m, kq) loads row m of column kq of a slice.  Rows past
+        // the panel read the next column's values into tile rows that are
+        // never stored: four neighbouring lanes of which some are out of
+        // range take the slow path of the load unit.
+        // FP64: an 8-byte load costs the unit as much as one of 16, so lane
+        // (m, kq) loads rows 2 (m % 8) and 2 (m % 8) + 1 of column 2 kq + m / 8
+        // of the group's 8 columns in one, and lanes m and m + 8 then exchange
+        // halves (fill_pair below): slice u of a group holds its columns
+        // 2 kq + u, tile row m the panel row tile_row(m).
+        const uint32_t vlane = PAIR ? (uint32_t)((2 * kq + (m >> 3)) * b + mt * 16 + 2 * (m & 7)) * 8u
+                                    : (uint32_t)(kq * b + p) * (uint32_t)sizeof(T);
         // XB: all of X lies within 2^31 bytes and is read through one buffer
         // descriptor (cheaper addressing); otherwise through 64-bit pointers
         const __amdgpu_buffer_rsrc_t rx =
             panel_rsrc(P.X, XB ? x_span(P) : 0u);
-        const uint32_t xcol = (uint32_t)(c0 + (VX ? VEC * m : m)) * sizeof(T);
+        // column part of the lane's offsets, per 16-byte load (VX) or tile.
+        // 4-byte loads: four neighbouring lanes are in range together (see
+        // the values above); those past nrhs read what follows inside X's
+        // span into output columns that are never stored.
+        uint32_t xcol[VX ? NL : NT];
+#pragma unroll
+        for (int l = 0; l < (VX ? NL : NT); ++l) {
+          const int c = VX ? c0 + l * 16 * VEC + VEC * m : c0 + l * 16 + m;
+          const int cq = !VX && sizeof(T) == 4 ? c & ~3 : c;
+          xcol[l] = cq < P.nrhs ? (uint32_t)c * (uint32_t)sizeof(T) : kOutCol;
+        }
         // lane (m, kq) loads the index of column kq of slice m / 8 (equal
         // addresses in every group of four lanes); the lanes of a row (equal
         // kq) then read slice u's from lane 8 u
         static_assert(U == 2, "one index register serves two slices");
+        auto col_of = [&](int g, int u) {   // panel column of slice u, lane row kq
+          return PAIR ? g * 8 + 2 * kq + u : (g * U + u) * 4 + kq;
+        };
         auto ld_idx = [&](int g) {
-          const int k = (g * U + (m >> 3)) * 4 + kq;
+          const int k = col_of(g, m >> 3);
           return (int32_t)__builtin_amdgcn_raw_buffer_load_b32(rc, (uint32_t)k * 4, 0, 0);
         };
-        // 4-byte loads of right-hand sides: four neighbouring lanes are in
-        // range together (see the values above); those past nrhs read what
-        // follows inside X's span into output columns that are never stored
-        const int mq = sizeof(T) == 4 ? m & ~3 : m;
-        auto ld_val = [&](int g, T(&av)[U]) {
+        // AUX 2: streamed past the caches; 0: kept, for the panel's next tile
+        // of rows (b > 16: FP64 b = 9..20 nrhs 16 200 -> 177 us; on b <= 16
+        // streaming is 2-5 % faster)
+        auto ld_val = [&](auto aux, int g, T(&av)[U]) {
+          constexpr int AUX = decltype(aux)::value;
+          if constexpr (PAIR) {
+            const double2 q = __builtin_bit_cast(
+                double2,
+                __builtin_amdgcn_raw_buffer_load_b128(rv, vlane + (uint32_t)(g * 8 * b) * 8u, 0, AUX));
+            av[0] = q.x;
+            av[1] = q.y;
+          } else {
 #pragma unroll
-          for (int u = 0; u < U; ++u)
-            av[u] = buf_load_nt<T>(rv, vlane + (uint32_t)((g * U + u) * 4 * b) * sizeof(T));
+            for (int u = 0; u < U; ++u) {
+              const uint32_t off = vlane + (uint32_t)((g * U + u) * 4 * b) * (uint32_t)sizeof(T);
+              av[u] = AUX ? buf_load_nt<T>(rv, off) : buf_load<T>(rv, off);
+            }
+          }
         };
         auto ld_x = [&](int g, int32_t xg, T(&xv)[U][NT]) {
           // XB: byte offset of the lane's own column, past the descriptor for
           // a padding column (reads zeros).  The product is formed before the
           // broadcast: after it the compiler fuses it with the addition of
-          // xcol into a 64-bit one whose unused upper half can be a register
+          // the column part into a 64-bit one whose unused upper half can be a register
           // with a load in flight, and waits for that load.
           const int32_t xo =
-              XB ? ((g * U + (m >> 3)) * 4 + kq < K
+              XB ? (col_of(g, m >> 3) < K
                         ? (int32_t)(uint32_t)((int64_t)xg * P.ldx * (int64_t)sizeof(T))
-                        : (int32_t)kOut)
+                        : (int32_t)kOutRow)
                  : xg;
           const int32_t xi[U] = {row_bcast<0>(xo), row_bcast<8>(xo)};
 #pragma unroll
           for (int u = 0; u < U; ++u) {
             if constexpr (XB) {
-              const uint32_t ro = (uint32_t)xi[u] + xcol;
+              const uint32_t ro = (uint32_t)xi[u];
               if constexpr (VX) {
 #pragma unroll
                 for (int l = 0; l < (VX ? NL : 1); ++l) {
                   const L16 q = __builtin_bit_cast(
-                      L16, __builtin_amdgcn_raw_buffer_load_b128(rx, ro + l * 16 * VEC * sizeof(T), 0, 0));
+                      L16, __builtin_amdgcn_raw_buffer_load_b128(rx, ro + xcol[l], 0, 0));
                   const T *qe = reinterpret_cast<const T *>(&q);
 #pragma unroll
                   for (int e = 0; e < VEC; ++e) xv[u][l * VEC + e] = qe[e];
@@ -673,11 +947,11 @@ __global__ void __launch_bounds__(kThreads) k_spmm_mfma(FwdParams<T> P) {
               } else {
 #pragma unroll
                 for (int t = 0; t < NT; ++t)
-                  xv[u][t] = buf_load<T>(rx, c0 + t * 16 + mq < P.nrhs ? ro + t * 16 * sizeof(T) : kOut);
+                  xv[u][t] = buf_load<T>(rx, ro + xcol[t]);
               }
             } else {
               // padding slices read a row of zeros instead of a row of X
-              const T *xp = (g * U + u) * 4 + kq < K ? P.X + (int64_t)xi[u] * P.ldx + c0 : zero_row<T>();
+              const T *xp = col_of(g, u) < K ? P.X + (int64_t)xi[u] * P.ldx + c0 : zero_row<T>();
               if constexpr (VX) {
 #pragma unroll
                 for (int l = 0; l < (VX ? NL : 1); ++l) {
@@ -696,47 +970,60 @@ __global__ void __launch_bounds__(kThreads) k_spmm_mfma(FwdParams<T> P) {
             }
           }
         };
-        auto mma = [&](const T(&av)[U], const T(&xv)[U][NT]) {
+        auto mma = [&](const T(&lv)[U], const T(&xv)[U][NT]) {
+          T av[U];
+          if constexpr (PAIR) {
+            fill_pair(lv[0], lv[1], av[0], av[1]);
+          } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u) av[u] = lv[u];
+          }
 #pragma unroll
           for (int u = 0; u < U; ++u)
 #pragma unroll
             for (int t = 0; t < NT; ++t) acc[t] = mfma(av[u], xv[u][t], acc[t]);
         };
         const int ngroups = (nsteps + U - 1) / U;
-        T av[R][U], xv[R][U][NT];
-        int32_t xi[R];
+        auto panel = [&](auto aux) {
+          T av[R][U], xv[R][U][NT];
+          int32_t xi[R];
 #pragma unroll
-        for (int r = 0; r < R; ++r) xi[r] = ld_idx(r);
+          for (int r = 0; r < R; ++r) xi[r] = ld_idx(r);
 #pragma unroll
-        for (int r = 0; r + 1 < R; ++r) {
-          ld_x(r, xi[r], xv[r]);
-          ld_val(r, av[r]);
-          xi[r] = ld_idx(r + R);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        int g = 0;
-        for (; g + R <= ngroups; g += R) {
-#pragma unroll
-          for (int r = 0; r < R; ++r) {
-            const int q = (r + R - 1) % R;
-            ld_x(g + r + R - 1, xi[q], xv[q]);
-            ld_val(g + r + R - 1, av[q]);
-            xi[q] = ld_idx(g + r + 2 * R - 1);
-            __builtin_amdgcn_sched_barrier(0);
-            mma(av[r], xv[r]);
-            __builtin_amdgcn_sched_barrier(0);
+          for (int r = 0; r + 1 < R; ++r) {
+            ld_x(r, xi[r], xv[r]);
+            ld_val(aux, r, av[r]);
+            xi[r] = ld_idx(r + R);
           }
-        }
+          __builtin_amdgcn_sched_barrier(0);
+          int g = 0;
+          for (; g + R <= ngroups; g += R) {
 #pragma unroll
-        for (int r = 0; r + 1 < R; ++r)
-          if (g + r < ngroups) mma(av[r], xv[r]);
+            for (int r = 0; r < R; ++r) {
+              const int q = (r + R - 1) % R;
+              ld_x(g + r + R - 1, xi[q], xv[q]);
+              ld_val(aux, g + r + R - 1, av[q]);
+              xi[q] = ld_idx(g + r + 2 * R - 1);
+              __builtin_amdgcn_sched_barrier(0);
+              mma(av[r], xv[r]);
+              __builtin_amdgcn_sched_barrier(0);
+            }
+          }
+#pragma unroll
+          for (int r = 0; r + 1 < R; ++r)
+            if (g + r < ngroups) mma(av[r], xv[r]);
+        };
+        if (b > 16)
+          panel(std::integral_constant<int, 0>{});
+        else
+          panel(std::integral_constant<int, 2>{});
         // epilogue: row pr of the tile, columns col(t)
         double mmv[NT];
 #pragma unroll
         for (int t = 0; t < NT; ++t) mmv[t] = 0.0;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const int pr = mt * 16 + dst_row<T>(kq, i);
+          const int pr = mt * 16 + (PAIR ? tile_row(dst_row<T>(kq, i)) : dst_row<T>(kq, i));
           if (pr < b) {
             const int64_t r = (int64_t)rd.yrow + pr;
             T y[NT];
@@ -746,6 +1033,18 @@ __global__ void __launch_bounds__(kThreads) k_spmm_mfma(FwdParams<T> P) {
 #pragma unroll
               for (int l = 0; l < (VX ? NL : 1); ++l) {
                 const int64_t cc = c0 + l * 16 * VEC + VEC * m;
+                if (!P.yrow16 || cc + VEC > P.nrhs) {   // element by element
+#pragma unroll
+                  for (int e = 0; e < VEC; ++e) {
+                    if (cc + e < P.nrhs) {
+                      T &ye = y[l * VEC + e];
+                      if (P.beta != 0.0) ye = fma(T(P.beta), P.Yin[r * P.ldyin + cc + e], ye);
+                      P.Yout[r * P.ldy + cc + e] = ye;
+                      if (MOM) mmv[l * VEC + e] += (double)P.R[r * P.ldr + cc + e] * (double)ye;
+                    }
+                  }
+                  continue;
+                }
                 if (P.beta != 0.0) {
                   const L16 q = *reinterpret_cast<const L16 *>(P.Yin + r * P.ldyin + cc);
                   const T *qe = reinterpret_cast<const T *>(&q);
@@ -856,7 +1155,13 @@ __global__ void __launch_bounds__(kThreads) k_spmm_bf16x3(FwdParams<float> P) {
         v4f acc[NT];
 #pragma unroll
         for (int t = 0; t < NT; ++t) acc[t] = v4f{};
-        const uint32_t xcol = (uint32_t)(c0 + m) * sizeof(float);
+        // four neighbouring lanes are in range together (as in the FP32 kernel)
+        uint32_t xcol[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+          const int c = c0 + t * 16 + m;
+          xcol[t] = (c & ~3) < P.nrhs ? (uint32_t)c * 4u : kOutCol;
+        }
         auto ld_idx = [&](int s) {
           // lane (m, kg) loads column m % 8 of its group; the lanes of a row
           // (equal kg) then read column u's from lane u
@@ -873,7 +1178,7 @@ __global__ void __launch_bounds__(kThreads) k_spmm_bf16x3(FwdParams<float> P) {
           const int32_t xo =
               XB ? (k0 + (m & 7) < K
                         ? (int32_t)(uint32_t)((int64_t)xg * P.ldx * (int64_t)sizeof(float))
-                        : (int32_t)kOut)
+                        : (int32_t)kOutRow)
                  : xg;
           const int32_t xi[8] = {row_bcast<0>(xo), row_bcast<1>(xo), row_bcast<2>(xo),
                                  row_bcast<3>(xo), row_bcast<4>(xo), row_bcast<5>(xo),
@@ -883,11 +1188,7 @@ __global__ void __launch_bounds__(kThreads) k_spmm_bf16x3(FwdParams<float> P) {
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
               if constexpr (XB) {
-                // padding columns read zeros; four neighbouring lanes are in
-                // range together (as in the FP32 kernel)
-                xv[t][u] = buf_load<float>(rx, c0 + t * 16 + (m & ~3) < P.nrhs
-                                                   ? (uint32_t)xi[u] + xcol + t * 64u
-                                                   : kOut);
+                xv[t][u] = buf_load<float>(rx, (uint32_t)xi[u] + xcol[t]);
               } else {
                 const int n = c0 + t * 16 + m;
                 const float *xp = k0 + u < K && n < P.nrhs ? P.X + (int64_t)xi[u] * P.ldx + n
@@ -1974,32 +2275,39 @@ hipError_t launch_mfma_xb(const FwdParams<T> &p, hipStream_t s, dim3 grid, size_
   return hipGetLastError();
 }
 
-template <typename T, int NT, bool VX>
-hipError_t launch_mfma_nt(const FwdParams<T> &p, hipStream_t s, dim3 grid, size_t shm) {
-  // one buffer descriptor covers X when its rows span less than 2^31 bytes
-  if (p.xrows * p.ldx * (int64_t)sizeof(T) < (int64_t(1) << 31))
-    return launch_mfma_xb<T, NT, VX, true>(p, s, grid, shm);
-  return launch_mfma_xb<T, NT, VX, false>(p, s, grid, shm);
+// Whether the rows that the epilogue reads and writes start on 16-byte
+// boundaries, and (vectorizable) the rows of X too, with the right-hand sides
+// filling whole passes.
+template <typename T>
+bool out_rows16(const FwdParams<T> &p) {
+  constexpr int VEC = 16 / sizeof(T);
+  auto al = [](const void *q) { return (reinterpret_cast<uintptr_t>(q) & 15) == 0; };
+  return al(p.Yout) && p.ldy % VEC == 0 && (p.beta == 0.0 || (al(p.Yin) && p.ldyin % VEC == 0)) &&
+         (!p.mom || (al(p.R) && p.ldr % VEC == 0));
 }
-
-// The vectorised fast path applies when every vector is 16-byte aligned,
-// every leading dimension is a multiple of the 16-byte element count and the
-// right-hand sides fill whole passes.
 template <typename T>
 bool vectorizable(const FwdParams<T> &p, int nt) {
   constexpr int VEC = 16 / sizeof(T);
-  auto al = [](const void *q) { return (reinterpret_cast<uintptr_t>(q) & 15) == 0; };
-  if (p.nrhs % (16 * nt) != 0) return false;
-  if (!al(p.X) || !al(p.Yout) || (p.beta != 0.0 && !al(p.Yin)) || (p.mom && !al(p.R))) return false;
-  if (p.ldx % VEC || p.ldy % VEC || (p.beta != 0.0 && p.ldyin % VEC) || (p.mom && p.ldr % VEC))
-    return false;
-  return true;
+  return p.nrhs % (16 * nt) == 0 && (reinterpret_cast<uintptr_t>(p.X) & 15) == 0 &&
+         p.ldx % VEC == 0 && out_rows16(p);
+}
+
+template <typename T, int NT>
+hipError_t launch_mfma_nt(const FwdParams<T> &p0, hipStream_t s, dim3 grid, size_t shm) {
+  FwdParams<T> p = p0;
+  p.yrow16 = out_rows16(p) ? 1 : 0;
+  constexpr bool V = NT % (16 / (int)sizeof(T)) == 0;   // tiles fill 16-byte loads
+  if (p.xrows * p.ldx * (int64_t)sizeof(T) < kXSpan)
+    return launch_mfma_xb<T, NT, V, true>(p, s, grid, shm);
+  if constexpr (V) {
+    if (vectorizable(p, NT)) return launch_mfma_xb<T, NT, true, false>(p, s, grid, shm);
+  }
+  return launch_mfma_xb<T, NT, false, false>(p, s, grid, shm);
 }
 
 template <int NT>
 hipError_t launch_bf16_nt(const FwdParams<float> &p, hipStream_t s, dim3 grid, size_t shm) {
-  // one buffer descriptor covers X when its rows span less than 2^31 bytes
-  const bool xb = p.xrows * p.ldx * (int64_t)sizeof(float) < (int64_t(1) << 31);
+  const bool xb = p.xrows * p.ldx * (int64_t)sizeof(float) < kXSpan;
   if (p.mom) {
     if (xb)
       hipLaunchKernelGGL((k_spmm_bf16x3<NT, true, true>), grid, dim3(kThreads), shm, s, p);
@@ -2014,12 +2322,46 @@ hipError_t launch_bf16_nt(const FwdParams<float> &p, hipStream_t s, dim3 grid, s
   return hipGetLastError();
 }
 
+template <int NG, int LW, int R>
+hipError_t launch_small_nr(const FwdParams<double> &p, hipStream_t s, dim3 grid, size_t shm) {
+  if (p.mom)
+    hipLaunchKernelGGL((k_spmm_small<NG, LW, true, R>), grid, dim3(kThreads), shm, s, p);
+  else
+    hipLaunchKernelGGL((k_spmm_small<NG, LW, false, R>), grid, dim3(kThreads), 0, s, p);
+  return hipGetLastError();
+}
+
+hipError_t launch_small(const FwdParams<double> &p0, hipStream_t s, dim3 grid, size_t shm) {
+  FwdParams<double> p = p0;
+  p.yrow16 = out_rows16(p) ? 1 : 0;
+  // registers allow deeper rings only where a step is narrow: R = 3 against 2
+  // is 4 % better on b = 8 at 3 right-hand sides and 14 % worse on b = 1/4/9
+  // at 16
+  if (p.nrhs <= 4) return launch_small_nr<1, 1, 3>(p, s, grid, shm);
+  if (p.nrhs <= 8) return launch_small_nr<2, 2, 2>(p, s, grid, shm);
+  if (p.nrhs <= 16) return launch_small_nr<4, 2, 2>(p, s, grid, shm);
+  return launch_small_nr<8, 2, 2>(p, s, grid, shm);
+}
+
 template <typename T>
 hipError_t launch_spmm_t(const FwdParams<T> &p, Kind kind, int tile, hipStream_t s) {
   const int64_t nwg = product_workgroups(p.nrows);
   if (nwg == 0) return hipSuccess;
   const dim3 grid((unsigned)nwg);
   const size_t shm = p.mom ? sizeof(double) * kWaves * (size_t)p.nrhs : 0;
+  if constexpr (std::is_same<T, double>::value) {
+    if (kind == Kind::Small) {
+      if (p.xrows * p.ldx * (int64_t)sizeof(T) < kXSpan) return launch_small(p, s, grid, shm);
+      // X beyond one buffer descriptor: the kernels with 64-bit addresses
+      if (p.nrhs <= 8) {
+        kind = Kind::Vec;
+        tile = p.nrhs <= 2 ? 2 : p.nrhs <= 4 ? 4 : 8;
+      } else {
+        kind = Kind::Mfma;
+        tile = p.nrhs <= 16 ? 1 : 2;
+      }
+    }
+  }
   if (kind == Kind::Vec) {
     switch (tile) {
       case 1: return launch_vec_nr<T, 1>(p, s, grid, shm);
@@ -2053,17 +2395,10 @@ hipError_t launch_spmm_t(const FwdParams<T> &p, Kind kind, int tile, hipStream_t
     }
   }
   // matrix cores: tile = right-hand-side tiles of 16 per pass
-  constexpr int VEC = 16 / sizeof(T);
-  if (tile >= VEC && vectorizable(p, tile)) {
-    if constexpr (VEC == 2) {
-      if (tile == 2) return launch_mfma_nt<T, 2, true>(p, s, grid, shm);
-    }
-    return launch_mfma_nt<T, 4, true>(p, s, grid, shm);
-  }
   switch (tile) {
-    case 1: return launch_mfma_nt<T, 1, false>(p, s, grid, shm);
-    case 2: return launch_mfma_nt<T, 2, false>(p, s, grid, shm);
-    default: return launch_mfma_nt<T, 4, false>(p, s, grid, shm);
+    case 1: return launch_mfma_nt<T, 1>(p, s, grid, shm);
+    case 2: return launch_mfma_nt<T, 2>(p, s, grid, shm);
+    default: return launch_mfma_nt<T, 4>(p, s, grid, shm);
   }
 }
 

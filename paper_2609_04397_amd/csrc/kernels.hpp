@@ -30,6 +30,7 @@ struct FwdParams {
   int64_t ldx;
   int64_t xrows;        // rows of X (columns of the operator)
   int32_t xrow16;       // set by the launcher: X rows start on 16-byte boundaries
+  int32_t yrow16;       // set by the launcher: so do the rows the epilogue touches
   const T *Yin;
   int64_t ldyin;
   T *Yout;
@@ -42,7 +43,7 @@ struct FwdParams {
 };
 
 // Kernel family and tiling chosen by the router.
-enum class Kind { Vec, Mfma, Bf16x3 };
+enum class Kind { Vec, Small, Mfma, Bf16x3 };
 
 // Number of workgroups a product launch over `nrows` panels uses (the
 // moment partials have this many rows).
