@@ -370,19 +370,6 @@ int require_square(const vbcsr_mat *A, const char *where) {
   return VBCSR_OK;
 }
 
-// Rows that 16-row tiles take for panels of these heights over those that
-// 4-row tiles take (1 to 4): what the small tiles save.
-template <typename It>
-double pad_ratio(It first, It last) {
-  int64_t r16 = 0, r4 = 0;
-  for (; first != last; ++first) {
-    const int64_t b = *first;
-    r16 += (b + 15) / 16 * 16;
-    r4 += (b + 3) / 4 * 4;
-  }
-  return r4 ? (double)r16 / (double)r4 : 1.0;
-}
-
 struct Route {
   Kind kind;
   int tile;

@@ -3,21 +3,15 @@
 // equation 1 with the conjugate transpose).
 #include <hip/hip_runtime.h>
 
+#include "device.hpp"
 #include "zkernels.hpp"
 
 namespace vbcsr {
 namespace {
 
-constexpr int kWaves = 4;
-constexpr int kThreads = 64 * kWaves;
-
 template <typename T> struct C2;
 template <> struct C2<double> { using type = double2; };
 template <> struct C2<float> { using type = float2; };
-
-__device__ __forceinline__ int wave_id() {
-  return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-}
 
 __global__ void __launch_bounds__(kThreads) k_zphase(ZPhaseParams P) {
   const int64_t c = (int64_t)blockIdx.x * kThreads + threadIdx.x;
@@ -123,7 +117,7 @@ __global__ void __launch_bounds__(kThreads) k_zsample(ZSampleParams P, T *fwd, T
 template <typename T, int NR>
 __global__ void __launch_bounds__(kThreads) k_zspmm(ZSpmmParams<T> P) {
   using V = typename C2<T>::type;
-  const int row = blockIdx.x * kWaves + wave_id();
+  const int row = xcd_remap(blockIdx.x, gridDim.x) * kWaves + wave_id();
   if (row >= P.nrows) return;
   const int lane = threadIdx.x & 63;
   const RowDesc rd = P.rows[row];
@@ -203,85 +197,241 @@ __global__ void __launch_bounds__(kThreads) k_zspmm(ZSpmmParams<T> P) {
   }
 }
 
-// Complex product on FP64 matrix cores, for 16 right-hand sides per tile:
-// one wave per panel, M = panel rows in tiles of 16, K = panel columns in
-// slices of 4, N = 16 right-hand sides per tile, NT tiles per pass.  Lane
-// (m, kq) loads 16 bytes of A (row m, column 4s + kq: one complex value) and,
-// per tile, 16 bytes of X (row colx[4s + kq], right-hand side m); four real
-// products per complex tile accumulate Ar Xr, Ai Xi, Ar Xi, Ai Xr.  Rows past
-// the panel, columns past K and right-hand sides past nrhs read zeros
-// through the buffer bounds.  The next slice's operands are in flight while
-// the current one multiplies.
 typedef double v4d __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t zrsrc(const void *base, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), (short)0, (int)bytes,
-                                           0x00020000);
-}
-__device__ __forceinline__ double2 zload(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+// One complex value in one load, widened to FP64.
+template <typename T> __device__ __forceinline__ double2 zload(__amdgpu_buffer_rsrc_t r, uint32_t off);
+template <> __device__ __forceinline__ double2 zload<double>(__amdgpu_buffer_rsrc_t r, uint32_t off) {
   return __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
 }
+template <> __device__ __forceinline__ double2 zload<float>(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+  const float2 v = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
+  return double2{(double)v.x, (double)v.y};
+}
 
-template <int NT>
+// y = alpha s + beta y for one complex element (y unread when beta is 0).
+template <typename T>
+__device__ __forceinline__ void zstore(const ZSpmmParams<T> &P, int64_t r, int c, double sr, double si) {
+  using V = typename C2<T>::type;
+  V *yp = reinterpret_cast<V *>(P.Y) + r * P.ldy + c;
+  double yr = P.ar * sr - P.ai * si, yi = P.ar * si + P.ai * sr;
+  if (P.br != 0.0 || P.bi != 0.0) {
+    const V y = *yp;
+    yr += P.br * (double)y.x - P.bi * (double)y.y;
+    yi += P.br * (double)y.y + P.bi * (double)y.x;
+  }
+  V o;
+  o.x = (T)yr;
+  o.y = (T)yi;
+  *yp = o;
+}
+
+// Complex product on small FP64 matrix-core tiles, 4 NG right-hand sides per
+// pass: the four 4x4 blocks of v_mfma_f64_4x4x4 take 4 panel rows x 4 panel
+// columns each (a step is 16 columns), so rows pad to 4 only.  Lane
+// 16 k + 4 q + i works on column 4 k + q and on row i of a row group (values)
+// or right-hand side i of a group (X); one load brings one complex value.
+// Four real products per complex one go to two accumulators (the imaginary
+// part of the value enters the real one negated); FP32 pages and vectors are
+// widened on load and accumulate in FP64.  A ring of R register sets: the
+// next R - 1 steps are in flight, their indices R further ahead; an index is
+// compared with the panel's end where it is used (at the load it would be
+// waited for).  The blocks' partial sums meet once per panel.
+// Bound by the load path (16 cycles of a compute unit per load): O(k) of the
+// b = 1/4/9 cube of 20 000 atoms, 16 right-hand sides, 98 us against 181 us
+// with 16-row tiles, whose matrix work was mostly padding; R = 3 110 us.
+template <typename T, int RG, int NG, int R>
+__device__ __forceinline__ void zsmall_rows(const ZSpmmParams<T> &P, const RowDesc &rd, int m0, int c0,
+                                            uint32_t xbytes) {
+  constexpr uint32_t ES = 2 * sizeof(T);
+  const int lane = threadIdx.x & 63;
+  const int ij = lane & 3;
+  const int col = 4 * (lane >> 4) + ((lane >> 2) & 3);
+  const int b = rd.b, K = rd.K;
+  const __amdgpu_buffer_rsrc_t ra = panel_rsrc(P.pages + 2 * rd.vbase, (uint32_t)K * (uint32_t)b * ES);
+  const __amdgpu_buffer_rsrc_t rc = panel_rsrc(P.colx + rd.cbase, (uint32_t)K * 4u);
+  const __amdgpu_buffer_rsrc_t rx = panel_rsrc(P.X, xbytes);
+  double re[RG][NG], im[RG][NG];
+#pragma unroll
+  for (int g = 0; g < RG; ++g)
+#pragma unroll
+    for (int t = 0; t < NG; ++t) re[g][t] = im[g][t] = 0.0;
+  const uint32_t vo = (uint32_t)(col * b + m0 + ij) * ES, vstep = (uint32_t)(16 * b) * ES;
+  uint32_t xcol[NG];
+#pragma unroll
+  for (int t = 0; t < NG; ++t) {
+    const int c = c0 + 4 * t + ij;
+    xcol[t] = c < P.nrhs ? (uint32_t)c * ES : kOutCol;
+  }
+  auto ld_idx = [&](int s) {
+    return (int32_t)__builtin_amdgcn_raw_buffer_load_b32(rc, (uint32_t)(16 * s + col) * 4, 0, 0);
+  };
+  auto ld = [&](int s, int32_t xi, double2 (&a)[RG], double2 (&x)[NG]) {
+    const uint32_t ro =
+        16 * s + col < K ? (uint32_t)((int64_t)xi * P.ldx * (int64_t)ES) : kOutRow;
+#pragma unroll
+    for (int t = 0; t < NG; ++t) x[t] = zload<T>(rx, ro + xcol[t]);
+    // rows past the panel read the next column's values into sums that are
+    // never stored
+#pragma unroll
+    for (int g = 0; g < RG; ++g) a[g] = zload<T>(ra, vo + (uint32_t)s * vstep + 4u * ES * g);
+  };
+  auto mma = [&](const double2 (&a)[RG], const double2 (&x)[NG]) {
+#pragma unroll
+    for (int g = 0; g < RG; ++g)
+#pragma unroll
+      for (int t = 0; t < NG; ++t) {
+        re[g][t] = __builtin_amdgcn_mfma_f64_4x4x4f64(a[g].x, x[t].x, re[g][t], 0, 0, 0);
+        im[g][t] = __builtin_amdgcn_mfma_f64_4x4x4f64(a[g].x, x[t].y, im[g][t], 0, 0, 0);
+      }
+#pragma unroll
+    for (int g = 0; g < RG; ++g) {
+      const double n = -a[g].y;
+#pragma unroll
+      for (int t = 0; t < NG; ++t) {
+        re[g][t] = __builtin_amdgcn_mfma_f64_4x4x4f64(n, x[t].y, re[g][t], 0, 0, 0);
+        im[g][t] = __builtin_amdgcn_mfma_f64_4x4x4f64(a[g].y, x[t].x, im[g][t], 0, 0, 0);
+      }
+    }
+  };
+  const int ns = (K + 15) >> 4;
+  double2 av[R][RG], xv[R][NG];
+  int32_t xi[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) xi[r] = ld_idx(r);
+#pragma unroll
+  for (int r = 0; r + 1 < R; ++r) {
+    ld(r, xi[r], av[r], xv[r]);
+    xi[r] = ld_idx(r + R);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  int s = 0;
+  for (; s + R <= ns; s += R) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int q = (r + R - 1) % R;
+      ld(s + r + R - 1, xi[q], av[q], xv[q]);
+      xi[q] = ld_idx(s + r + 2 * R - 1);
+      __builtin_amdgcn_sched_barrier(0);
+      mma(av[r], xv[r]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+#pragma unroll
+  for (int r = 0; r + 1 < R; ++r)
+    if (s + r < ns) mma(av[r], xv[r]);
+  // lane 16 i + 4 g + j writes row 4 g + i, right-hand sides j of each group
+  const int gl = (lane >> 2) & 3;
+  const int prow = m0 + 4 * gl + (lane >> 4);
+#pragma unroll
+  for (int t = 0; t < NG; ++t) {
+    double sr = 0.0, si = 0.0;
+#pragma unroll
+    for (int g = 0; g < RG; ++g) {
+      double u = re[g][t], v = im[g][t];
+      u += __shfl_xor(u, 4, 64);
+      u += __shfl_xor(u, 8, 64);
+      v += __shfl_xor(v, 4, 64);
+      v += __shfl_xor(v, 8, 64);
+      sr = gl == g ? u : sr;
+      si = gl == g ? v : si;
+    }
+    const int c = c0 + 4 * t + ij;
+    if (gl < RG && prow < b && c < P.nrhs) zstore(P, (int64_t)rd.yrow + prow, c, sr, si);
+  }
+}
+
+template <typename T, int NG, int R>
+__global__ void __launch_bounds__(kThreads) k_zspmm_small(ZSpmmParams<T> P, uint32_t xbytes) {
+  const int row = xcd_remap(blockIdx.x, gridDim.x) * kWaves + wave_id();
+  if (row >= P.nrows) return;
+  const RowDesc rd = P.rows[row];
+  for (int c0 = 0; c0 < P.nrhs; c0 += 4 * NG)
+    for (int m0 = 0; m0 < rd.b; m0 += 16) {
+      switch ((min(rd.b - m0, 16) + 3) >> 2) {
+        case 1: zsmall_rows<T, 1, NG, R>(P, rd, m0, c0, xbytes); break;
+        case 2: zsmall_rows<T, 2, NG, R>(P, rd, m0, c0, xbytes); break;
+        case 3: zsmall_rows<T, 3, NG, R>(P, rd, m0, c0, xbytes); break;
+        default: zsmall_rows<T, 4, NG, R>(P, rd, m0, c0, xbytes); break;
+      }
+    }
+}
+
+// Complex product on 16x16x4 FP64 matrix cores, for more than 16 right-hand
+// sides: one wave per panel, M = panel rows in tiles of 16, K = panel columns
+// in slices of 4, N = 16 right-hand sides per tile, NT tiles per pass.  Lane
+// (m, kq) loads 16 bytes of A (row m, column 4s + kq: one complex value) and,
+// per tile, 16 bytes of X; accumulators, ring and padding as above.
+template <int NT, int R>
 __global__ void __launch_bounds__(kThreads) k_zspmm_mfma(ZSpmmParams<double> P, uint32_t xbytes) {
-  const int row = blockIdx.x * kWaves + wave_id();
+  const int row = xcd_remap(blockIdx.x, gridDim.x) * kWaves + wave_id();
   if (row >= P.nrows) return;
   const int lane = threadIdx.x & 63;
   const int m = lane & 15, kq = lane >> 4;
   const RowDesc rd = P.rows[row];
   const int b = rd.b, K = rd.K;
-  constexpr uint32_t kOut = 0x80000000u;
-  const __amdgpu_buffer_rsrc_t ra = zrsrc(reinterpret_cast<const double2 *>(P.pages) + rd.vbase,
-                                          (uint32_t)K * (uint32_t)b * 16u);
-  const __amdgpu_buffer_rsrc_t rx = zrsrc(P.X, xbytes);
-  const int32_t *__restrict__ cx = P.colx + rd.cbase;
+  const __amdgpu_buffer_rsrc_t ra = panel_rsrc(P.pages + 2 * rd.vbase, (uint32_t)K * (uint32_t)b * 16u);
+  const __amdgpu_buffer_rsrc_t rc = panel_rsrc(P.colx + rd.cbase, (uint32_t)K * 4u);
+  const __amdgpu_buffer_rsrc_t rx = panel_rsrc(P.X, xbytes);
   const int nsl = (K + 3) >> 2;
-  double2 *__restrict__ Y = reinterpret_cast<double2 *>(P.Y);
   for (int mt = 0; mt * 16 < b; ++mt) {
-    const int ar = mt * 16 + m;
+    const uint32_t vo = (uint32_t)(kq * b + mt * 16 + m) * 16u, vstep = (uint32_t)(4 * b) * 16u;
     for (int c0 = 0; c0 < P.nrhs; c0 += 16 * NT) {
-      v4d rr[NT], ii[NT], ri[NT], ir[NT];
+      v4d re[NT], im[NT];
+      uint32_t xcol[NT];
 #pragma unroll
-      for (int t = 0; t < NT; ++t) rr[t] = ii[t] = ri[t] = ir[t] = v4d{0.0, 0.0, 0.0, 0.0};
-      // three stages: the column index of slice s + 2, the values and X rows
-      // of slice s + 1 (whose index arrived one slice earlier), the matrix
-      // instructions of slice s; slices past the end repeat the last one
+      for (int t = 0; t < NT; ++t) {
+        re[t] = im[t] = v4d{0.0, 0.0, 0.0, 0.0};
+        const int c = c0 + 16 * t + m;
+        xcol[t] = c < P.nrhs ? (uint32_t)c * 16u : kOutCol;
+      }
       auto ld_idx = [&](int s) {
-        const int k = 4 * s + kq;
-        return k < K ? cx[min(k, K - 1)] : -1;
+        return (int32_t)__builtin_amdgcn_raw_buffer_load_b32(rc, (uint32_t)(4 * s + kq) * 4, 0, 0);
       };
-      auto ld = [&](int s, int xr, double2 &a, double2 (&x)[NT]) {
-        const int k = 4 * s + kq;
-        a = zload(ra, ar < b ? (uint32_t)(k * b + ar) * 16u : kOut);
+      auto ld = [&](int s, int32_t xi, double2 &a, double2 (&x)[NT]) {
+        const uint32_t ro = 4 * s + kq < K ? (uint32_t)((int64_t)xi * P.ldx * 16) : kOutRow;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) x[t] = zload<double>(rx, ro + xcol[t]);
+        a = zload<double>(ra, vo + (uint32_t)s * vstep);
+      };
+      auto mma = [&](const double2 &a, const double2 (&x)[NT]) {
+        const double n = -a.y;
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
-          const int c = c0 + t * 16 + m;
-          x[t] = zload(rx, xr >= 0 && c < P.nrhs
-                                ? (uint32_t)(((int64_t)xr * P.ldx + c) * 16)
-                                : kOut);
+          re[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, x[t].x, re[t], 0, 0, 0);
+          im[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, x[t].y, im[t], 0, 0, 0);
+        }
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+          re[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(n, x[t].y, re[t], 0, 0, 0);
+          im[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, x[t].x, im[t], 0, 0, 0);
         }
       };
-      if (nsl > 0) {
-        double2 a, x[NT];
-        int xi1 = ld_idx(min(1, nsl - 1));
-        ld(0, ld_idx(0), a, x);
-        for (int s = 0; s < nsl; ++s) {
-          const int xi2 = ld_idx(min(s + 2, nsl - 1));
-          double2 an, xn[NT];
-          ld(min(s + 1, nsl - 1), xi1, an, xn);
+      double2 av[R], xv[R][NT];
+      int32_t xi[R];
 #pragma unroll
-          for (int t = 0; t < NT; ++t) {
-            rr[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, x[t].x, rr[t], 0, 0, 0);
-            ii[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, x[t].y, ii[t], 0, 0, 0);
-            ri[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, x[t].y, ri[t], 0, 0, 0);
-            ir[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, x[t].x, ir[t], 0, 0, 0);
-          }
-          a = an;
+      for (int r = 0; r < R; ++r) xi[r] = ld_idx(r);
 #pragma unroll
-          for (int t = 0; t < NT; ++t) x[t] = xn[t];
-          xi1 = xi2;
+      for (int r = 0; r + 1 < R; ++r) {
+        ld(r, xi[r], av[r], xv[r]);
+        xi[r] = ld_idx(r + R);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      int s = 0;
+      for (; s + R <= nsl; s += R) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const int q = (r + R - 1) % R;
+          ld(s + r + R - 1, xi[q], av[q], xv[q]);
+          xi[q] = ld_idx(s + r + 2 * R - 1);
+          __builtin_amdgcn_sched_barrier(0);
+          mma(av[r], xv[r]);
+          __builtin_amdgcn_sched_barrier(0);
         }
       }
+#pragma unroll
+      for (int r = 0; r + 1 < R; ++r)
+        if (s + r < nsl) mma(av[r], xv[r]);
       // accumulator element e of quarter-wave kq: tile row kq + 4e, column m
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
@@ -289,17 +439,7 @@ __global__ void __launch_bounds__(kThreads) k_zspmm_mfma(ZSpmmParams<double> P, 
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const int r = mt * 16 + kq + 4 * e;
-          if (r < b && c < P.nrhs) {
-            const double sr = rr[t][e] - ii[t][e], si = ri[t][e] + ir[t][e];
-            double2 *yp = Y + (int64_t)(rd.yrow + r) * P.ldy + c;
-            double yr = P.ar * sr - P.ai * si, yi = P.ar * si + P.ai * sr;
-            if (P.br != 0.0 || P.bi != 0.0) {
-              const double2 y = *yp;
-              yr += P.br * y.x - P.bi * y.y;
-              yi += P.br * y.y + P.bi * y.x;
-            }
-            *yp = double2{yr, yi};
-          }
+          if (r < b && c < P.nrhs) zstore(P, (int64_t)rd.yrow + r, c, re[t][e], im[t][e]);
         }
       }
     }
@@ -365,23 +505,44 @@ hipError_t launch_zsample(const ZSampleParams &p, void *fwd, void *tr, int elem_
   return hipGetLastError();
 }
 
-hipError_t launch_zspmm_f64(const ZSpmmParams<double> &p, hipStream_t s) {
-  // 16 or more right-hand sides go to matrix cores when X spans less than
-  // 2^31 bytes (one buffer descriptor with 32-bit offsets)
-  const int64_t xspan = ((int64_t)p.xrows - 1) * p.ldx + p.nrhs;
-  if (p.nrhs < 16 || p.nrows == 0 || xspan * 16 >= (int64_t(1) << 31)) return launch_zspmm_t(p, s);
+// Matrix cores when X spans less than one buffer descriptor (kXSpan), else
+// the vector kernel with 64-bit addresses.  Small tiles for every operator up
+// to 16 right-hand sides and in FP32 (vector kernel against small tiles, FP64
+// O(k) of the b = 1/4/9 cube of 20 000 atoms: 51 against 43 us at 1, 77/49 at
+// 4, 196/66 at 8; FP32 42/37 at 1, 99/55 at 8, 201/94 at 16, 385/180 at 32;
+// 16-row tiles against small tiles at 16: 181/98).  FP64 beyond 16: small
+// tiles where 16-row tiles pad much (b = 1/4/9, ratio 1.9: 204 us against 162
+// at 24, 386/239 at 40, 388/330 at 64), 16-row tiles where they pad less
+// (b = 9/20, ratio 1.4: 316 against 331 at 20, 331/364 at 32, 591/787 at 64).
+template <typename T>
+hipError_t launch_zspmm_any(const ZSpmmParams<T> &p, hipStream_t s) {
+  const int64_t xbytes = (((int64_t)p.xrows - 1) * p.ldx + p.nrhs) * 2 * (int64_t)sizeof(T);
+  if (p.nrows == 0 || xbytes >= kXSpan) return launch_zspmm_t(p, s);
   const dim3 grid((unsigned)((p.nrows + kWaves - 1) / kWaves));
-  const uint32_t xb = (uint32_t)(xspan * 16);
-  if (p.nrhs <= 16)
-    hipLaunchKernelGGL(k_zspmm_mfma<1>, grid, dim3(kThreads), 0, s, p, xb);
-  else if (p.nrhs <= 32)
-    hipLaunchKernelGGL(k_zspmm_mfma<2>, grid, dim3(kThreads), 0, s, p, xb);
+  const uint32_t xb = (uint32_t)xbytes;
+  if constexpr (sizeof(T) == 8) {
+    if (p.nrhs > 16 && p.pad16 <= 1.6) {
+      if (p.nrhs <= 32)
+        hipLaunchKernelGGL((k_zspmm_mfma<2, 4>), grid, dim3(kThreads), 0, s, p, xb);
+      else
+        hipLaunchKernelGGL((k_zspmm_mfma<4, 3>), grid, dim3(kThreads), 0, s, p, xb);
+      return hipGetLastError();
+    }
+  }
+  if (p.nrhs <= 4)
+    hipLaunchKernelGGL((k_zspmm_small<T, 1, 2>), grid, dim3(kThreads), 0, s, p, xb);
+  else if (p.nrhs <= 8)
+    hipLaunchKernelGGL((k_zspmm_small<T, 2, 2>), grid, dim3(kThreads), 0, s, p, xb);
   else
-    hipLaunchKernelGGL(k_zspmm_mfma<4>, grid, dim3(kThreads), 0, s, p, xb);
+    hipLaunchKernelGGL((k_zspmm_small<T, 4, 2>), grid, dim3(kThreads), 0, s, p, xb);
   return hipGetLastError();
 }
+
+hipError_t launch_zspmm_f64(const ZSpmmParams<double> &p, hipStream_t s) {
+  return launch_zspmm_any(p, s);
+}
 hipError_t launch_zspmm_f32(const ZSpmmParams<float> &p, hipStream_t s) {
-  return launch_zspmm_t(p, s);
+  return launch_zspmm_any(p, s);
 }
 
 hipError_t launch_zunpack(const void *fwd, int elem_bytes, const int64_t *pos,
