@@ -262,6 +262,7 @@ int env_path() {
 
 struct vbcsr_mat {
   int32_t n = 0;       // atoms: block columns (and block rows when square)
+  int32_t bmax = VBCSR_MAX_BLOCK;  // largest block size
   int32_t n_rows = 0;  // block rows: n, or the owned atoms of a rank-local operator
   int64_t N = 0, N_rows = 0, nnzb = 0, nnz = 0;
   int32_t n_shapes = 0;
@@ -576,6 +577,7 @@ int create_impl(vbcsr_mat **out, int32_t n_atoms, const int32_t *block_sizes,
   if ((rc = upload_into(A, &A->col_idx, col_idx, (size_t)plan.nnzb, s))) return bail(rc);
   if ((rc = upload_into(A, &A->blk_row, plan.blk_row, s))) return bail(rc);
   if ((rc = upload_into(A, &A->gbase, plan.gbase.data(), (size_t)plan.nnzb, s))) return bail(rc);
+  A->bmax = n_atoms ? *std::max_element(block_sizes, block_sizes + n_atoms) : 1;
   for (int d = 0; d < 2; ++d) {
     const DirPlan &P = d == 0 ? plan.fwd : plan.tr;
     DevDir &D = A->dir[d];
@@ -691,6 +693,7 @@ int create_planned_on_device(vbcsr_mat **out, const vbcsr_mat *A, int64_t nnzb, 
     return fail(VBCSR_EUNSUPPORTED, "a block column of the product holds 2^28 or more values");
   C->nnz = po.nnz;
   C->n_shapes = po.n_shapes;
+  C->bmax = A->bmax;
   for (int d = 0; d < 2; ++d) {
     DevDir &D = C->dir[d];
     D.n_values = po.dir[d].n_values;
@@ -879,12 +882,12 @@ int vbcsr_sddmm(const vbcsr_mat *A, const void *dY, int64_t lddy, const void *X,
   if (A->prec == VBCSR_FP64) {
     SddmmParams<double> p{D.rows, D.npanels, D.colx, D.colg, static_cast<const double *>(dY), lddy,
                           static_cast<const double *>(X), ldx, nrhs, static_cast<double *>(dA),
-                          A->N};
+                          A->N, 0, A->bmax};
     err = launch_sddmm_f64(p, s);
   } else {
     SddmmParams<float> p{D.rows, D.npanels, D.colx, D.colg, static_cast<const float *>(dY), lddy,
                          static_cast<const float *>(X), ldx, nrhs, static_cast<float *>(dA),
-                         A->N};
+                         A->N, 0, A->bmax};
     err = launch_sddmm_f32(p, s);
   }
   if (err != hipSuccess) return hip_fail(err, "sddmm kernel launch");
@@ -999,12 +1002,12 @@ int vbcsr_sddmm_pages(const vbcsr_mat *A, const void *dY, int64_t lddy, const vo
     if (A->prec == VBCSR_FP64) {
       SddmmParams<double> p{D.rows, D.npanels, D.colx, D.colg, static_cast<const double *>(dY),
                             lddy, static_cast<const double *>(X), ldx, nrhs,
-                            static_cast<double *>(dA), A->N, 1};
+                            static_cast<double *>(dA), A->N, 1, A->bmax};
       err = launch_sddmm_f64(p, s);
     } else {
       SddmmParams<float> p{D.rows, D.npanels, D.colx, D.colg, static_cast<const float *>(dY),
                            lddy, static_cast<const float *>(X), ldx, nrhs,
-                           static_cast<float *>(dA), A->N, 1};
+                           static_cast<float *>(dA), A->N, 1, A->bmax};
       err = launch_sddmm_f32(p, s);
     }
     if (err != hipSuccess) return hip_fail(err, "sddmm kernel launch");

@@ -139,6 +139,16 @@ __device__ __forceinline__ int32_t row_bcast(int32_t v) {
   return __builtin_amdgcn_update_dpp(0, v, 0x150 + U, 0xF, 0xF, false);
 }
 
+// Value of lane 4 q + u of the caller's four lanes q to all of them (u constant).
+__device__ __forceinline__ int32_t quad_bcast(int32_t v, int u) {
+  switch (u) {
+    case 0: return __builtin_amdgcn_update_dpp(0, v, 0x00, 0xF, 0xF, false);
+    case 1: return __builtin_amdgcn_update_dpp(0, v, 0x55, 0xF, 0xF, false);
+    case 2: return __builtin_amdgcn_update_dpp(0, v, 0xAA, 0xF, 0xF, false);
+    default: return __builtin_amdgcn_update_dpp(0, v, 0xFF, 0xF, 0xF, false);
+  }
+}
+
 // 64 zeros, read in place of an X row where a lane has none (padding slices,
 // columns past a staged chunk, right-hand sides past nrhs); any T of <= 8 bytes
 __device__ __align__(16) double kZeroRow[64] = {};  // never written
@@ -1834,324 +1844,285 @@ __global__ void __launch_bounds__(kThreads) k_sddmm_lds(SddmmParams<T> P) {
 }
 
 // ---------------------------------------------------------------------------
-// block-sampled dY X^T in FP64 with the X rows loaded straight into LDS
+// block-sampled dY X^T, X rows loaded straight into LDS, outputs through LDS
 // ---------------------------------------------------------------------------
-// Same products, accumulation order and output map as k_sddmm_mfma, for
-// nrhs = 32 NCH.  A step is one tile and one 32-wide chunk of right-hand
-// sides.  Its 16 X row pieces (256 bytes each) go from memory to a 4 KiB
+// One wave per panel, up to 64 right-hand sides: 16 panel rows x 16 panel
+// columns per tile on matrix cores.  A step is one tile and one chunk of PR
+// 16-byte pieces of right-hand sides (NCH chunks); its 16 X row pieces go to a
 // wave-private LDS buffer by buffer-to-LDS loads, which hold no registers
-// while in flight; the next step's loads are issued as soon as the current
-// B fragments are in registers, so they overlap this step's matrix
-// instructions.  A tile's outputs are stored during the first step of the
-// next tile, from a second accumulator pair, after that step's loads are
-// issued: the wait for the loads of a step never waits on stores issued
-// after them.
+// while in flight, adjacent lanes reading adjacent pieces of a row (a load
+// whose neighbouring lanes read different rows costs four times the tag
+// lookups: X straight to registers in fragment order took 324 us where this
+// takes 299).  The next step's loads are issued as soon as the fragments are
+// in registers.  Lane (m, kq) holds pieces kq + 4 h of row m for both operands.
 //
-// LDS layout: load instruction it (0..3) writes 64 lanes x 16 bytes to
-// consecutive addresses; lane l (q = l >> 4) fetches row r = 4 q + it, piece
-// (l & 15) ^ r, so row r sits at (r & 3) * 1 KiB + (r >> 2) * 256 bytes with
-// its pieces permuted, and the fragment reads of 16 rows at one piece index
-// hit 16 distinct bank groups.  Lane l reads the X row indices of its four
-// rows with one 16-byte load (rows past the panel are not loaded).  Column indices and output maps are loaded two tiles ahead.
-// Requires X within 2^31 bytes (one buffer descriptor).
-// PAGE: outputs in the forward pages' layout (P.page_out), where a tile's
-// outputs are one contiguous run and nothing is held back.
-template <int NCH, bool PAGE>
-__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) k_sddmm_dma(SddmmParams<double> P) {
+// Stores scattered from the accumulators bound the kernel (20 L2 writes and
+// half the load unit's time per tile), so outputs go through LDS and leave in
+// output order.  PAGE (the forward pages' layout): a tile's outputs are one
+// run, stored 16 bytes a lane.  Graph order: a ring of RS outputs in panel
+// order (block by block, each row-major) with their graph offsets; whole
+// blocks are stored, 64 NS outputs a tile, a block that runs on into the next
+// tile waits for its end.  At most (bj - 1) b wait as a block's first columns
+// and as many for their turn, and a tile spans up to 16 + 2 (bj - 1) columns'
+// outputs: b (3 bmax + 13) <= RS keeps them apart.  NS = 0 stores straight from
+// the accumulators: panels that the ring does not hold (a ring of 1024 leaves
+// two workgroups a compute unit: b = 13, 64 right-hand sides, 77 us against
+// 66).  NS < 0 does so by 64-bit addresses (panels of 1 GiB and more).
+//
+// b = 1/4/9, K about 150: 32 right-hand sides, FP32, 100 000 panels, graph
+// order 357 -> 299 us, pages 287 -> 238; FP64, 50 000 panels 302 -> 262 and
+// 236 -> 224; 40 right-hand sides FP64 546 -> 394; b = 4/9, 8000 panels, 7
+// right-hand sides, FP64, pages 87 -> 31.
+template <typename T, int PR, int NCH, bool PAGE, int RS, int NS>
+__device__ __forceinline__ void sddmm_panel(const SddmmParams<T> &P, const RowDesc &rd, int m0,
+                                            uint32_t xbytes, T *xs, T *ring, int32_t *aring) {
   using LdsPtr = __attribute__((address_space(3))) void *;
-  constexpr int CW = 32;
-  __shared__ __align__(16) double xs_all[kWaves * 16 * CW];
-  const int row = xcd_remap(blockIdx.x, gridDim.x) * kWaves + wave_id();
-  if (row >= P.nrows) return;
+  using V = typename Frag<T>::type;
+  using L16 = typename Vec16<T>::type;
+  constexpr int EPL = 16 / (int)sizeof(T);   // elements of a piece
+  constexpr uint32_t ES = sizeof(T);
+  constexpr int NIT = PR / 4;                // load instructions of a step
   const int lane = threadIdx.x & 63;
-  const int m = lane & 15;
-  const int kq = lane >> 4;
-  double *xs = xs_all + wave_id() * 16 * CW;
-  const RowDesc rd = P.rows[row];
+  const int m = lane & 15, kq = lane >> 4;
   const int b = rd.b, K = rd.K;
-  if (K == 0) return;
-  const int ntiles = (K + 15) >> 4;
-  const int nsteps = ntiles * NCH;
-  const int64_t *__restrict__ cg = P.colg + rd.cbase;
-  const __amdgpu_buffer_rsrc_t rx =
-      panel_rsrc(P.X, (uint32_t)(P.xrows * P.ldx * (int64_t)sizeof(double)));
-  // the panel's indices rounded up to a group of four (the table has four
-  // entries of slack), so a group is either wholly in range or wholly past it
-  const __amdgpu_buffer_rsrc_t rc =
-      panel_rsrc(P.colx + rd.cbase, (uint32_t)((K + 3) & ~3) * 4u);
-  // X row indices of rows 4 kq .. 4 kq + 3 of tile j
+  const __amdgpu_buffer_rsrc_t rc = panel_rsrc(P.colx + rd.cbase, (uint32_t)K * 4u);
+  const __amdgpu_buffer_rsrc_t rg = panel_rsrc(PAGE ? nullptr : P.colg + rd.cbase, (uint32_t)K * 8u);
+  const __amdgpu_buffer_rsrc_t rx = panel_rsrc(P.X, xbytes);
+  // graph offset of the panel's first column; outputs lie within b K of it
+  const int64_t g0 = PAGE ? 0 : P.colg[rd.cbase] >> 7;
+  const uint32_t bk = (uint32_t)b * (uint32_t)K;
+  const __amdgpu_buffer_rsrc_t ro =
+      PAGE ? panel_rsrc(P.dA + rd.vbase, ((bk + 3) & ~3u) * ES)
+           : panel_rsrc(P.dA + (g0 - (int64_t)bk), NS < 0 ? 0 : 2 * bk * ES);
+  // the 64 / PR lane groups (group = lane / PR) stage rows NIT group + it of a
+  // tile with load it; lane i of every four loads the index of row NIT group + i
+  const int grp = lane / PR;
   auto rows_of = [&](int j) {
-    return __builtin_bit_cast(v4u32, __builtin_amdgcn_raw_buffer_load_b128(
-                                         rc, (uint32_t)(j * 16 + 4 * kq) * 4u, 0, 0));
+    return __builtin_amdgcn_raw_buffer_load_b32(rc, (uint32_t)(16 * j + NIT * grp + (lane & 3)) * 4u, 0, 0);
   };
   auto gmap_of = [&](int j) {
-    const int kk = min(j * 16 + m, K - 1);
-    return PAGE ? page_map(rd, kk) : cg[kk];
+    if constexpr (PAGE)
+      return v2u32{0u, 0u};
+    else
+      return __builtin_bit_cast(v2u32, __builtin_amdgcn_raw_buffer_load_b64(rg, (uint32_t)(16 * j + m) * 8u, 0, 0));
   };
-  const int sslot = lane & 15;
-  auto issue = [&](int s, v4u32 xr) {
-    const int j = s / NCH, ch = s % NCH;
+  // pieces sit permuted in their LDS row, so that one piece index of the 16
+  // rows covers all banks
+  auto perm = [](int r) { return PR == 16 ? r : PR == 8 ? ((r >> 2) << 1 | (r & 1)) : r >> 2; };
+  uint32_t xcol[NCH][NIT];
 #pragma unroll
-    for (int it = 0; it < 4; ++it) {
-      const int r = 4 * kq + it;
-      const int pc = sslot ^ r;
-      const uint32_t off =
-          j * 16 + r < K ? (uint32_t)(((int64_t)(int32_t)xr[it] * P.ldx + ch * CW + 2 * pc) *
-                                      (int64_t)sizeof(double))
-                         : 0x80000000u;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (LdsPtr)(xs + it * 4 * CW), 16, off, 0, 0, 0);
+  for (int ch = 0; ch < NCH; ++ch)
+#pragma unroll
+    for (int it = 0; it < NIT; ++it) {
+      const int c = EPL * (PR * ch + ((lane % PR) ^ perm(NIT * grp + it)));
+      xcol[ch][it] = c < P.nrhs ? (uint32_t)c * ES : kOutCol;
     }
+  auto issue = [&](int j, int ch, int32_t xi) {
+    const int32_t xo = 16 * j + NIT * grp + (lane & 3) < K
+                           ? (int32_t)(uint32_t)((int64_t)xi * P.ldx * (int64_t)ES)
+                           : (int32_t)kOutRow;
+#pragma unroll
+    for (int it = 0; it < NIT; ++it)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (LdsPtr)(xs + it * 64 * EPL), 16,
+                                               (uint32_t)quad_bcast(xo, it) + xcol[ch][it], 0, 0, 0);
   };
-  const double *xm = xs + (m & 3) * 4 * CW + (m >> 2) * CW;   // row m in LDS
-  for (int mt = 0; mt * 16 < b; ++mt) {
-    const int p = mt * 16 + m;
-    const double *dyrow = P.dY + ((int64_t)rd.yrow + (p < b ? p : b - 1)) * P.lddy;
-    // A fragments: lane (m, kq) holds c = 32 ch + 8 l + 2 kq + e (l < 4, e < 2)
-    double af[NCH][8];
+  // dY: rows past the panel and right-hand sides past nrhs are zero
+  T af[NCH][NIT][EPL];
+  {
+    const __amdgpu_buffer_rsrc_t rdy =
+        panel_rsrc(P.dY + (int64_t)rd.yrow * P.lddy, (uint32_t)((b - 1) * P.lddy + P.nrhs) * ES);
+    const uint32_t yo = m0 + m < b ? (uint32_t)((m0 + m) * P.lddy) * ES : kOutRow;
 #pragma unroll
     for (int ch = 0; ch < NCH; ++ch)
 #pragma unroll
-      for (int s = 0; s < 8; ++s) {
-        const double v = dyrow[ch * CW + 2 * kq + 8 * (s >> 1) + (s & 1)];
-        af[ch][s] = p < b ? v : 0.0;
+      for (int h = 0; h < NIT; ++h) {
+        const int c = EPL * (PR * ch + 4 * h + kq);
+        const L16 v = __builtin_bit_cast(
+            L16, __builtin_amdgcn_raw_buffer_load_b128(rdy, yo + (c < P.nrhs ? (uint32_t)c * ES : kOutCol), 0, 0));
+#pragma unroll
+        for (int e = 0; e < EPL; ++e)
+          af[ch][h][e] = c + e < P.nrhs ? reinterpret_cast<const T *>(&v)[e] : T(0);
       }
-    // index registers: tiles j (cur), j + 1 (nxt), j + 2 (nn, loaded during
-    // tile j); they move along at the start of a tile, after the step's wait,
-    // so no copy waits on a load in flight
-    v4u32 xr_cur = rows_of(0), xr_nxt = rows_of(1), xr_nn = xr_nxt;
-    int64_t g_cur = gmap_of(0), g_nxt = gmap_of(1), g_nn = g_nxt, g_done = 0, g_carry = 0;
-    issue(0, xr_cur);
-    v4d acc0 = v4d{}, acc1 = v4d{};
-    double done[4] = {0.0, 0.0, 0.0, 0.0}, carry[4] = {0.0, 0.0, 0.0, 0.0};
-    int csplit = 16;   // lanes m >= csplit hold carried outputs of the tile before
-    for (int j = 0; j < ntiles; ++j) {
+  }
+  const bool ragged = P.nrhs % EPL != 0;
+  const int nt = (K + 15) >> 4;
+  int sprev = 0, F = 0;        // first column of the block at a tile's start; outputs flushed
+  int32_t uprev = -1;
+  // graph offset of a column relative to g0 (at most a panel's size: 32 bits)
+  auto rel = [&](const v2u32 &g) {
+    return (int32_t)(__builtin_amdgcn_alignbit(g.y, g.x, 7) - (uint32_t)g0);
+  };
+  // every lane issues its stores, those without an output past the range
+  // (no store): the number of stores in flight is then known at each wait
+  auto put = [&](T v, uint32_t e, bool ok) {
+    const uint32_t off = e * ES | (ok ? 0u : 0xF0000000u);
+    if constexpr (sizeof(T) == 8)
+      __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2u32, v), ro, off, 0, 0);
+    else
+      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), ro, off, 0, 0);
+  };
+  auto flush = [&](int e, int E) {
+    const T v = ring[e & (RS - 1)];
+    put(v, (uint32_t)aring[e & (RS - 1)], e < E);
+  };
+  auto out = [&](int j, const V &acc, const v2u32 &g, const v2u32 &gn) {
+    const int k = 16 * j + m;
+    if constexpr (PAGE && NS > 0) {
 #pragma unroll
-      for (int ch = 0; ch < NCH; ++ch) {
-        const int s = j * NCH + ch;
-        double bv[8];
+      for (int i = 0; i < 4; ++i) {
+        const int p = dst_row<T>(kq, i);
+        if (p < b) ring[m * b + p] = acc[i];
+      }
+      wave_lds_sync();
+      const uint32_t nst = (uint32_t)(min(K - 16 * j, 16) * b);
 #pragma unroll
-        for (int l = 0; l < 4; ++l) {
-          const double2 v = *reinterpret_cast<const double2 *>(xm + 2 * ((kq + 4 * l) ^ m));
-          bv[2 * l] = v.x;
-          bv[2 * l + 1] = v.y;
+      for (int i = 0; i < NS; ++i) {
+        const uint32_t e = (uint32_t)EPL * (64 * i + lane);
+        L16 v = *reinterpret_cast<const L16 *>(ring + (e & (RS - 1)));
+        T *ve = reinterpret_cast<T *>(&v);
+#pragma unroll
+        for (int q = 0; q < EPL; ++q) ve[q] = e + q < nst ? ve[q] : T(0);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u32, v), ro,
+                                               e < nst ? (16u * j * b + e) * ES : 0xF0000000u, 0, 0);
+      }
+      wave_lds_sync();
+    } else if constexpr (NS > 0) {
+      const int32_t u = rel(g);
+      const int bj = (int)(g.x & 127);
+      const int32_t up = __builtin_amdgcn_update_dpp(uprev, u, 0x111, 0xF, 0xF, false);  // row_shr:1
+      const uint32_t brk = (uint32_t)__ballot(k < K && u != up + 1) & 0xFFFFu;
+      const uint32_t below = brk & ((2u << m) - 1u);
+      const int sc = below ? 16 * j + 31 - __builtin_clz(below) : sprev;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int p = dst_row<T>(kq, i);
+        if (p < b && k < K) {
+          const int at = (b * sc + p * bj + k - sc) & (RS - 1);
+          ring[at] = acc[i];
+          aring[at] = u + p * bj + (int32_t)bk;
         }
-        // the fragments are in registers before the buffer is refilled
-        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0); vmcnt, expcnt unchanged
-        if (ch == 0 && j > 0) {
+      }
+      wave_lds_sync();
+      sprev = __builtin_amdgcn_readlane(sc, 15);
+      uprev = __builtin_amdgcn_readlane(u, 15);
+      const bool cont = j + 1 < nt && __builtin_amdgcn_readlane(rel(gn), 0) == uprev + 1 && b > 1;
+      const int E = cont ? b * sprev : b * min(16 * (j + 1), K);
 #pragma unroll
-          for (int i = 0; i < 4; ++i) done[i] = acc0[i] + acc1[i];
-          acc0 = v4d{};
-          acc1 = v4d{};
-          g_done = g_cur;
-          xr_cur = xr_nxt;
-          g_cur = g_nxt;
-          xr_nxt = xr_nn;
-          g_nxt = g_nn;
-        }
-        if (s + 1 < nsteps) issue(s + 1, ch == NCH - 1 ? xr_nxt : xr_cur);
-        if (ch == 0) {
-          xr_nn = rows_of(j + 2);
-          g_nn = gmap_of(j + 2);
-          if (j > 0) {
-            // Outputs of tile j - 1 (a whole tile: j - 1 is not the last).
-            // A block whose columns run on into tile j is held back and
-            // stored with the rest of it after tile j, so that each block's
-            // lines are written in one burst.  split = first column of that
-            // block in tile j - 1 (16: none held back).
-            const uint32_t u = (uint32_t)(g_done >> 7);
-            const uint32_t up = __shfl(u, lane - 1, 64);
-            const bool brk = m == 0 || u != up + 1u;
-            const uint32_t u15 = __shfl(u, 15, 64);
-            const uint32_t unext = (uint32_t)(__shfl(g_cur, 0, 64) >> 7);
-            const uint32_t brks = (uint32_t)__ballot(brk) & 0xFFFFu;
-            const int split = !PAGE && unext == u15 + 1u ? 31 - __builtin_clz(brks) : 16;
-            if (m >= csplit) {
-              const int64_t base = g_carry >> 7;
-              const int bj = (int)(g_carry & 127);
+      for (int i = 0; i < NS; ++i) flush(F + 64 * i + lane, E);
+      F = min(E, F + 64 * NS);
+      wave_lds_sync();
+    } else if constexpr (NS == 0) {
+      const uint32_t a = PAGE ? (uint32_t)(k * b) : (uint32_t)rel(g) + bk;
+      const int bj = PAGE ? 1 : (int)(g.x & 127);
 #pragma unroll
-              for (int i = 0; i < 4; ++i) {
-                const int pr = mt * 16 + dst_row<double>(kq, i);
-                if (pr < b) P.dA[base + (int64_t)pr * bj] = carry[i];
-              }
-            }
-            if (m < split) {
-              const int64_t base = g_done >> 7;
-              const int bj = (int)(g_done & 127);
+      for (int i = 0; i < 4; ++i) {
+        const int p = m0 + dst_row<T>(kq, i);
+        put(acc[i], a + (uint32_t)(p * bj), p < b && k < K);
+      }
+    } else {
+      if (k < K) {
+        const int64_t a = PAGE ? rd.vbase + (int64_t)k * b : g0 + rel(g);
+        const int bj = PAGE ? 1 : (int)(g.x & 127);
 #pragma unroll
-              for (int i = 0; i < 4; ++i) {
-                const int pr = mt * 16 + dst_row<double>(kq, i);
-                if (pr < b) P.dA[base + (int64_t)pr * bj] = done[i];
-              }
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) carry[i] = done[i];
-            g_carry = g_done;
-            csplit = split;
-          }
-        }
-#pragma unroll
-        for (int l = 0; l < 8; l += 2) {
-          acc0 = mfma(af[ch][l], bv[l], acc0);
-          acc1 = mfma(af[ch][l + 1], bv[l + 1], acc1);
+        for (int i = 0; i < 4; ++i) {
+          const int p = m0 + dst_row<T>(kq, i);
+          if (p < b) P.dA[a + (int64_t)p * bj] = acc[i];
         }
       }
     }
-    // held-back outputs of the tile before the last, then the last tile
-    if (m >= csplit) {
-      const int64_t base = g_carry >> 7;
-      const int bj = (int)(g_carry & 127);
+  };
+  const T *xm = xs + ((m % NIT) * 64 + (m / NIT) * PR) * EPL;   // row m in LDS
+  // indices and maps of tile j + 1 are loaded ahead of tile j's X rows: they
+  // have arrived when the rows have, and move along then.  The fragments of a
+  // step are read at the end of the step before, after its stores: there the
+  // number of stores behind the rows' loads is known, and the wait for the
+  // rows leaves them in flight.
+  L16 bv[NIT];
+  auto fragments = [&] {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int pr = mt * 16 + dst_row<double>(kq, i);
-        if (pr < b) P.dA[base + (int64_t)pr * bj] = carry[i];
-      }
-    }
-    if ((ntiles - 1) * 16 + m < K) {
-      const int64_t base = g_cur >> 7;
-      const int bj = (int)(g_cur & 127);
+    for (int h = 0; h < NIT; ++h)
+      bv[h] = *reinterpret_cast<const L16 *>(xm + EPL * ((kq + 4 * h) ^ perm(m)));
+    // the fragments are in registers before the buffer is refilled
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0); vmcnt, expcnt unchanged
+  };
+  int32_t xn = rows_of(0), xc = xn;
+  v2u32 gc = v2u32{0u, 0u}, gx = gmap_of(0);
+  int32_t xl = rows_of(1);
+  v2u32 gl = gmap_of(1);
+  issue(0, 0, xn);
+  fragments();
+  for (int j = 0; j < nt; ++j) {
+    V acc0 = V{}, acc1 = V{};
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int pr = mt * 16 + dst_row<double>(kq, i);
-        if (pr < b) P.dA[base + (int64_t)pr * bj] = acc0[i] + acc1[i];
+    for (int ch = 0; ch < NCH; ++ch) {
+      if (ch == 0) {
+        gc = gx;
+        gx = gl;
+        xc = xn;
+        xn = xl;
       }
+      if (ch + 1 < NCH) {
+        issue(j, ch + 1, xc);
+      } else {
+        xl = rows_of(j + 2);
+        gl = gmap_of(j + 2);
+        issue(j + 1, 0, xn);
+      }
+#pragma unroll
+      for (int h = 0; h < NIT; ++h) {
+        const T *xe = reinterpret_cast<const T *>(&bv[h]);
+        const int c = EPL * (PR * ch + 4 * h + kq);
+#pragma unroll
+        for (int e = 0; e < EPL; e += 2) {
+          acc0 = mfma(af[ch][h][e], ragged && c + e >= P.nrhs ? T(0) : xe[e], acc0);
+          acc1 = mfma(af[ch][h][e + 1], ragged && c + e + 1 >= P.nrhs ? T(0) : xe[e + 1], acc1);
+        }
+      }
+      if (ch + 1 == NCH) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc0[i] += acc1[i];
+        out(j, acc0, gc, gx);
+      }
+      fragments();
     }
   }
+  if constexpr (!PAGE && NS > 0)
+    for (; F < (int)bk; F += 64) flush(F + lane, (int)bk);
 }
 
-// The same in FP32 (nrhs = 32 NCH): a step is one tile and one 32-wide chunk
-// of right-hand sides, whose 16 X row pieces (128 bytes each, 2 KiB) arrive
-// by two buffer-to-LDS loads: lane l of load it fetches 16-byte piece
-// (l & 7) ^ (r & 7) of row r = 8 it + (l >> 3), so row r sits at r * 128
-// bytes with its pieces permuted and the fragment reads of 16 rows at one
-// piece index spread over the banks.  Lane (m, kq) holds right-hand sides
-// 8 kq .. 8 kq + 7 of each chunk for both operands (two pieces of its row;
-// the contraction order inside a chunk is permuted, the sum is the same).
-// A tile's outputs are stored during the first step of the next tile, after
-// that step's loads are issued.  Requires X within 2^31 bytes, 16-byte
-// aligned rows.
-template <int NCH, bool PAGE>
-__global__ void __launch_bounds__(kThreads) k_sddmm_dma32(SddmmParams<float> P) {
-  using LdsPtr = __attribute__((address_space(3))) void *;
-  constexpr int CW = 32;
-  __shared__ __align__(16) float xs_all[kWaves * 16 * CW];
+template <typename T, int PR, int NCH, bool PAGE, int RS>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NCH == 2 ? 4 : 1)))
+k_sddmm(SddmmParams<T> P, uint32_t xbytes) {
+  constexpr int XE = 16 * PR * (16 / (int)sizeof(T));
+  __shared__ __align__(16) T xs_all[kWaves * XE];
+  __shared__ __align__(16) T ring_all[kWaves * RS];
+  __shared__ int32_t aring_all[PAGE ? 1 : kWaves * RS];
   const int row = xcd_remap(blockIdx.x, gridDim.x) * kWaves + wave_id();
   if (row >= P.nrows) return;
-  const int lane = threadIdx.x & 63;
-  const int m = lane & 15;
-  const int kq = lane >> 4;
-  float *xs = xs_all + wave_id() * 16 * CW;
   const RowDesc rd = P.rows[row];
-  const int b = rd.b, K = rd.K;
-  if (K == 0) return;
-  const int ntiles = (K + 15) >> 4;
-  const int nsteps = ntiles * NCH;
-  const int64_t *__restrict__ cg = P.colg + rd.cbase;
-  const __amdgpu_buffer_rsrc_t rx =
-      panel_rsrc(P.X, (uint32_t)(P.xrows * P.ldx * (int64_t)sizeof(float)));
-  // the panel's indices rounded up to a group of four (four entries of slack)
-  const __amdgpu_buffer_rsrc_t rc =
-      panel_rsrc(P.colx + rd.cbase, (uint32_t)((K + 3) & ~3) * 4u);
-  const int lr = lane >> 3;   // this lane's rows of a step: lr and 8 + lr
-  auto rows_of = [&](int j) {
-    v2u32 r;
-    r.x = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rc, (uint32_t)(j * 16 + lr) * 4u, 0, 0);
-    r.y = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rc, (uint32_t)(j * 16 + 8 + lr) * 4u, 0,
-                                                         0);
-    return r;
-  };
-  auto gmap_of = [&](int j) {
-    const int kk = min(j * 16 + m, K - 1);
-    return PAGE ? page_map(rd, kk) : cg[kk];
-  };
-  auto issue = [&](int s, v2u32 xr) {
-    const int j = s / NCH, ch = s % NCH;
-#pragma unroll
-    for (int it = 0; it < 2; ++it) {
-      const int r = 8 * it + lr;
-      const int pc = (lane & 7) ^ (r & 7);
-      const uint32_t off =
-          j * 16 + r < K ? (uint32_t)(((int64_t)(int32_t)xr[it] * P.ldx + ch * CW + 4 * pc) *
-                                      (int64_t)sizeof(float))
-                         : 0x80000000u;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (LdsPtr)(xs + it * 8 * CW), 16, off, 0, 0, 0);
-    }
-  };
-  const float *xm = xs + m * CW;   // row m in LDS
-  for (int mt = 0; mt * 16 < b; ++mt) {
-    const int p = mt * 16 + m;
-    const float *dyrow = P.dY + ((int64_t)rd.yrow + (p < b ? p : b - 1)) * P.lddy;
-    // A fragments: lane (m, kq) holds c = 32 ch + 8 kq + t
-    float af[NCH][8];
-#pragma unroll
-    for (int ch = 0; ch < NCH; ++ch)
-#pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        const float v = dyrow[ch * CW + 8 * kq + t];
-        af[ch][t] = p < b ? v : 0.0f;
-      }
-    v2u32 xr_cur = rows_of(0), xr_nxt = rows_of(1), xr_nn = xr_nxt;
-    int64_t g_cur = gmap_of(0), g_nxt = gmap_of(1), g_nn = g_nxt, g_done = 0;
-    issue(0, xr_cur);
-    v4f acc0 = v4f{}, acc1 = v4f{};
-    float done[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    for (int j = 0; j < ntiles; ++j) {
-#pragma unroll
-      for (int ch = 0; ch < NCH; ++ch) {
-        const int s = j * NCH + ch;
-        float bv[8];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const float4 v =
-              *reinterpret_cast<const float4 *>(xm + 4 * ((2 * kq + h) ^ (m & 7)));
-          bv[4 * h] = v.x;
-          bv[4 * h + 1] = v.y;
-          bv[4 * h + 2] = v.z;
-          bv[4 * h + 3] = v.w;
-        }
-        // the fragments are in registers before the buffer is refilled
-        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0); vmcnt, expcnt unchanged
-        if (ch == 0 && j > 0) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) done[i] = acc0[i] + acc1[i];
-          acc0 = v4f{};
-          acc1 = v4f{};
-          g_done = g_cur;
-          xr_cur = xr_nxt;
-          g_cur = g_nxt;
-          xr_nxt = xr_nn;
-          g_nxt = g_nn;
-        }
-        if (s + 1 < nsteps) issue(s + 1, ch == NCH - 1 ? xr_nxt : xr_cur);
-        if (ch == 0) {
-          xr_nn = rows_of(j + 2);
-          g_nn = gmap_of(j + 2);
-          if (j > 0) {   // outputs of tile j - 1 (a whole tile)
-            const int64_t base = g_done >> 7;
-            const int bj = (int)(g_done & 127);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              const int pr = mt * 16 + dst_row<float>(kq, i);
-              if (pr < b) P.dA[base + (int64_t)pr * bj] = done[i];
-            }
-          }
-        }
-#pragma unroll
-        for (int t = 0; t < 8; t += 2) {
-          acc0 = mfma(af[ch][t], bv[t], acc0);
-          acc1 = mfma(af[ch][t + 1], bv[t + 1], acc1);
-        }
-      }
-    }
-    // outputs of the last tile
-    if ((ntiles - 1) * 16 + m < K) {
-      const int64_t base = g_cur >> 7;
-      const int bj = (int)(g_cur & 127);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int pr = mt * 16 + dst_row<float>(kq, i);
-        if (pr < b) P.dA[base + (int64_t)pr * bj] = acc0[i] + acc1[i];
-      }
-    }
+  if (rd.K == 0) return;
+  T *xs = xs_all + wave_id() * XE, *ring = ring_all + wave_id() * RS;
+  int32_t *ra = aring_all + (PAGE ? 0 : wave_id() * RS);
+  const int b = rd.b;
+  const bool big = (int64_t)b * rd.K * (int64_t)sizeof(T) >= (int64_t(1) << 30);
+  if (big) {
+    for (int m0 = 0; m0 < b; m0 += 16)
+      sddmm_panel<T, PR, NCH, PAGE, RS, -1>(P, rd, m0, xbytes, xs, ring, ra);
+  } else if (PAGE ? b > 16 : b > 16 || b * (3 * P.bmax + 13) > RS) {
+    for (int m0 = 0; m0 < b; m0 += 16)
+      sddmm_panel<T, PR, NCH, PAGE, RS, 0>(P, rd, m0, xbytes, xs, ring, ra);
+  } else if constexpr (PAGE) {
+    if (sizeof(T) == 4 || b <= 8)
+      sddmm_panel<T, PR, NCH, PAGE, RS, 1>(P, rd, 0, xbytes, xs, ring, ra);
+    else
+      sddmm_panel<T, PR, NCH, PAGE, RS, 2>(P, rd, 0, xbytes, xs, ring, ra);
+  } else {
+    if (b <= 4)
+      sddmm_panel<T, PR, NCH, PAGE, RS, 1>(P, rd, 0, xbytes, xs, ring, ra);
+    else if (b <= 12)
+      sddmm_panel<T, PR, NCH, PAGE, RS, 3>(P, rd, 0, xbytes, xs, ring, ra);
+    else
+      sddmm_panel<T, PR, NCH, PAGE, RS, 4>(P, rd, 0, xbytes, xs, ring, ra);
   }
 }
 
@@ -2673,41 +2644,35 @@ hipError_t launch_pack(const PackParams &p, const void *src, int src_dtype, hipS
   return hipGetLastError();
 }
 
+template <typename T, int PR, int NCH>
+void launch_sddmm_tiles(const SddmmParams<T> &p, dim3 grid, uint32_t xbytes, hipStream_t s) {
+  if (p.page_out)
+    hipLaunchKernelGGL((k_sddmm<T, PR, NCH, true, 256>), grid, dim3(kThreads), 0, s, p, xbytes);
+  else
+    hipLaunchKernelGGL((k_sddmm<T, PR, NCH, false, 512>), grid, dim3(kThreads), 0, s, p, xbytes);
+}
+
 template <typename T>
 hipError_t launch_sddmm_t(const SddmmParams<T> &p, hipStream_t s) {
   if (p.nrows == 0) return hipSuccess;
   const dim3 grid((unsigned)product_workgroups(p.nrows));
-  // X rows staged through LDS when all of X fits one buffer descriptor
-  if (p.xrows * p.ldx * (int64_t)sizeof(T) < (int64_t(1) << 31)) {
-    if (std::is_same<T, double>::value && (p.nrhs == 32 || p.nrhs == 64)) {
-      const auto &pd = reinterpret_cast<const SddmmParams<double> &>(p);
-      if (p.nrhs == 32 && p.page_out)
-        hipLaunchKernelGGL((k_sddmm_dma<1, true>), grid, dim3(kThreads), 0, s, pd);
-      else if (p.nrhs == 32)
-        hipLaunchKernelGGL((k_sddmm_dma<1, false>), grid, dim3(kThreads), 0, s, pd);
-      else if (p.page_out)
-        hipLaunchKernelGGL((k_sddmm_dma<2, true>), grid, dim3(kThreads), 0, s, pd);
-      else
-        hipLaunchKernelGGL((k_sddmm_dma<2, false>), grid, dim3(kThreads), 0, s, pd);
-      return hipGetLastError();
-    }
-    if (std::is_same<T, float>::value && (p.nrhs == 32 || p.nrhs == 64) &&
-        reinterpret_cast<uintptr_t>(p.X) % 16 == 0 && p.ldx % 4 == 0) {
-      const auto &pf = reinterpret_cast<const SddmmParams<float> &>(p);
-      if (p.nrhs == 32 && p.page_out)
-        hipLaunchKernelGGL((k_sddmm_dma32<1, true>), grid, dim3(kThreads), 0, s, pf);
-      else if (p.nrhs == 32)
-        hipLaunchKernelGGL((k_sddmm_dma32<1, false>), grid, dim3(kThreads), 0, s, pf);
-      else if (p.page_out)
-        hipLaunchKernelGGL((k_sddmm_dma32<2, true>), grid, dim3(kThreads), 0, s, pf);
-      else
-        hipLaunchKernelGGL((k_sddmm_dma32<2, false>), grid, dim3(kThreads), 0, s, pf);
-      return hipGetLastError();
-    }
-    if (p.nrhs <= 32)
-      hipLaunchKernelGGL((k_sddmm_lds<T, 32>), grid, dim3(kThreads), 0, s, p);
-    else
-      hipLaunchKernelGGL((k_sddmm_lds<T, 64>), grid, dim3(kThreads), 0, s, p);
+  // X rows through LDS when X spans less than one buffer descriptor; up to 64
+  // right-hand sides in one pass (a panel's dY rows are addressed by 32 bits)
+  const int64_t xb = ((p.xrows - 1) * p.ldx + p.nrhs) * (int64_t)sizeof(T);
+  if (xb < kXSpan && p.nrhs <= 64 && p.lddy < (1 << 22)) {
+    const int pieces = (p.nrhs * (int)sizeof(T) + 15) / 16;
+    if (pieces <= 4)
+      launch_sddmm_tiles<T, 4, 1>(p, grid, (uint32_t)xb, s);
+    else if (pieces <= 8)
+      launch_sddmm_tiles<T, 8, 1>(p, grid, (uint32_t)xb, s);
+    else if (pieces <= 16)
+      launch_sddmm_tiles<T, 16, 1>(p, grid, (uint32_t)xb, s);
+    else if constexpr (sizeof(T) == 8)
+      launch_sddmm_tiles<T, 16, 2>(p, grid, (uint32_t)xb, s);
+    return hipGetLastError();
+  }
+  if (p.nrhs > 32 && p.xrows * p.ldx * (int64_t)sizeof(T) < (int64_t(1) << 31)) {
+    hipLaunchKernelGGL((k_sddmm_lds<T, 64>), grid, dim3(kThreads), 0, s, p);
     return hipGetLastError();
   }
   // right-hand sides beyond the register-resident chunks are loaded per tile
