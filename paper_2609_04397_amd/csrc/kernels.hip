@@ -1557,18 +1557,13 @@ __global__ void __launch_bounds__(kThreads) k_refresh_records(PackParams P, cons
   rec[u] = r;
 }
 
+// Blocks lane u < nb (record r) of a wave, column-major at the source, row-major
+// at the destination; the records go through `tab` (the wave's LDS).
 template <typename T>
-__global__ void __launch_bounds__(kThreads) k_refresh(const PageRec *rec, int64_t nnzb,
-                                                      const T *src, T *dst) {
-  __shared__ PageRec tab_all[kWaves * kPackRun];
-  const int64_t u0 = ((int64_t)blockIdx.x * kWaves + wave_id()) * kPackRun;
-  if (u0 >= nnzb) return;
-  const int lane = threadIdx.x & 63;
-  const int nb = (int)min((int64_t)kPackRun, nnzb - u0);
-  PageRec *tab = tab_all + wave_id() * kPackRun;
+__device__ __forceinline__ void transpose_run(const PageRec &r, PageRec *tab, int nb, int lane,
+                                              const T *src, T *dst) {
   int n = 0;
   if (lane < nb) {
-    const PageRec r = rec[u0 + lane];
     n = r.bi * r.bj;
     tab[lane] = r;
   }
@@ -1597,14 +1592,14 @@ __global__ void __launch_bounds__(kThreads) k_refresh(const PageRec *rec, int64_
           t = u;
           stt = st[u];
         }
-      const PageRec &r = tab[t];
-      const int b1 = r.bi, b2 = r.bj, l = e - stt;
+      const PageRec &q0 = tab[t];
+      const int b1 = q0.bi, b2 = q0.bj, l = e - stt;
       // element (p, q): row-major at the destination, column-major at the source
       int p = (int)((float)l * __builtin_amdgcn_rcpf((float)b2));
       int q = l - p * b2;
       if (q >= b2) { ++p; q -= b2; }
-      v[c] = src[r.src + (int64_t)q * b1 + p];
-      d[c] = r.dst + l;
+      v[c] = src[q0.src + (int64_t)q * b1 + p];
+      d[c] = q0.dst + l;
     }
 #pragma unroll
     for (int c = 0; c < kPackChunk; ++c) {
@@ -1612,6 +1607,19 @@ __global__ void __launch_bounds__(kThreads) k_refresh(const PageRec *rec, int64_
       dst[d[c]] = v[c];
     }
   }
+}
+
+template <typename T>
+__global__ void __launch_bounds__(kThreads) k_refresh(const PageRec *rec, int64_t nnzb,
+                                                      const T *src, T *dst) {
+  __shared__ PageRec tab_all[kWaves * kPackRun];
+  const int64_t u0 = ((int64_t)blockIdx.x * kWaves + wave_id()) * kPackRun;
+  if (u0 >= nnzb) return;
+  const int lane = threadIdx.x & 63;
+  const int nb = (int)min((int64_t)kPackRun, nnzb - u0);
+  PageRec r{};
+  if (lane < nb) r = rec[u0 + lane];
+  transpose_run<T>(r, tab_all + wave_id() * kPackRun, nb, lane, src, dst);
 }
 
 // ---------------------------------------------------------------------------
@@ -2535,23 +2543,30 @@ __global__ void __launch_bounds__(kThreads) k_gather_blocks(const double *src,
   for (int e = lane; e < size[t]; e += 64) dp[e] = sp[e];
 }
 
-// Forward pages -> graph order (each block row-major at gbase); one wave per
-// block.
+// Forward pages -> graph order (each block row-major at gbase): a wave takes
+// kPackRun blocks, whose values are one run of the destination (a million
+// blocks of 1, 4 and 9: 112 us, 374 with one block a wave; 775,000 blocks of
+// 9 to 20, 1.3 GB each way: 645 both ways, 4 TB/s, columns read 8 bytes a lane).
 template <typename T>
 __global__ void __launch_bounds__(kThreads) k_unpack(const T *pages, const int64_t *pos,
                                                      const int32_t *blk_row,
                                                      const int32_t *col_idx, const int32_t *b,
                                                      const int64_t *gbase, int64_t nnzb, T *dst) {
-  const int64_t k = (int64_t)blockIdx.x * kWaves + wave_id();
-  if (k >= nnzb) return;
+  __shared__ PageRec tab_all[kWaves * kPackRun];
+  const int64_t k0 = ((int64_t)blockIdx.x * kWaves + wave_id()) * kPackRun;
+  if (k0 >= nnzb) return;
   const int lane = threadIdx.x & 63;
-  const int bi = b[blk_row[k]], bj = b[col_idx[k]];
-  const T *sp = pages + pos[k];
-  T *dp = dst + gbase[k];
-  for (int e = lane; e < bi * bj; e += 64) {
-    const int p = e / bj, q = e - p * bj;
-    dp[e] = sp[(int64_t)q * bi + p];
+  const int nb = (int)min((int64_t)kPackRun, nnzb - k0);
+  PageRec *tab = tab_all + wave_id() * kPackRun;
+  PageRec r{};
+  if (lane < nb) {
+    const int64_t k = k0 + lane;
+    r.src = pos[k];
+    r.dst = gbase[k];
+    r.bi = b[blk_row[k]];
+    r.bj = b[col_idx[k]];
   }
+  transpose_run<T>(r, tab, nb, lane, pages, dst);
 }
 
 // ---------------------------------------------------------------------------
@@ -2601,18 +2616,22 @@ __global__ void __launch_bounds__(kThreads) k_kpm_dos(const double *c, int M, co
   if (i < np) rho[i] = s / (M_PI * sqrt(1.0 - xi * xi));
 }
 
-// One thread per graph block writes the column-table entries of its panel
-// columns (set-up, once per structure).
+// 16 lanes per graph block write the column-table entries of its panel columns
+// (set-up, once per structure): runs of b entries instead of one lane's
+// entries b apart (775,000 blocks of 9 to 20, both directions: 39 us
+// a call against 147).
 __global__ void __launch_bounds__(kThreads) k_columns(ColumnParams P) {
-  const int64_t k = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (k >= P.nnzb) return;
-  const int32_t c = P.catom[k];
-  const int bc = P.b[c];
-  const int64_t base = P.rows[P.prow[k]].cbase + P.k0[k];
-  const int32_t o = P.off[c];
-  for (int q = 0; q < bc; ++q) {
-    P.colx[base + q] = o + q;
-    if (P.colg) P.colg[base + q] = ((P.gbase[k] + q) << 7) | bc;
+  for (int64_t k = ((int64_t)blockIdx.x * kThreads + threadIdx.x) >> 4; k < P.nnzb;
+       k += (int64_t)gridDim.x * (kThreads / 16)) {
+    const int32_t c = P.catom[k];
+    const int bc = P.b[c];
+    const int64_t base = P.rows[P.prow[k]].cbase + P.k0[k];
+    const int32_t o = P.off[c];
+    const int64_t g = P.colg ? P.gbase[k] : 0;
+    for (int q = threadIdx.x & 15; q < bc; q += 16) {
+      P.colx[base + q] = o + q;
+      if (P.colg) P.colg[base + q] = ((g + q) << 7) | bc;
+    }
   }
 }
 
@@ -2808,7 +2827,8 @@ hipError_t launch_unpack(const void *pages, int elem_bytes, const int64_t *pos,
                          const int32_t *blk_row, const int32_t *col_idx, const int32_t *b,
                          const int64_t *gbase, int64_t nnzb, void *dst, hipStream_t s) {
   if (nnzb == 0) return hipSuccess;
-  const dim3 grid((unsigned)((nnzb + kWaves - 1) / kWaves));
+  const int64_t waves = (nnzb + kPackRun - 1) / kPackRun;
+  const dim3 grid((unsigned)((waves + kWaves - 1) / kWaves));
   if (elem_bytes == 8)
     hipLaunchKernelGGL(k_unpack<double>, grid, dim3(kThreads), 0, s,
                        static_cast<const double *>(pages), pos, blk_row, col_idx, b, gbase, nnzb,
@@ -2833,7 +2853,8 @@ hipError_t launch_kpm_dos(const double *mu, int M, int damping, const double *x,
 
 hipError_t launch_columns(const ColumnParams &p, hipStream_t s) {
   if (p.nnzb == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_columns, dim3((unsigned)((p.nnzb + kThreads - 1) / kThreads)), dim3(kThreads),
+  const int64_t lanes = std::min<int64_t>(16 * p.nnzb, int64_t(1) << 30);
+  hipLaunchKernelGGL(k_columns, dim3((unsigned)((lanes + kThreads - 1) / kThreads)), dim3(kThreads),
                      0, s, p);
   return hipGetLastError();
 }

@@ -17,6 +17,7 @@
 #include <hipcub/hipcub.hpp>
 
 #include "kernels.hpp"
+#include "sort.hpp"
 #include "../../include/vbcsr.h"
 
 namespace vbcsr {
@@ -61,12 +62,26 @@ __global__ void __launch_bounds__(kT) k_pd_keys(int64_t nnzb, int d, const int32
                                                 const int32_t *b, uint64_t *key, int32_t *val,
                                                 unsigned long long *width) {
   const int64_t k = (int64_t)blockIdx.x * kT + threadIdx.x;
-  if (k >= nnzb) return;
-  const int32_t r = d == 0 ? blk_row[k] : ci[k];
-  const int32_t c = d == 0 ? ci[k] : blk_row[k];
-  key[k] = (uint64_t)(uint32_t)rank[r] << 7 | (uint32_t)b[c];
-  val[k] = (int32_t)k;
-  atomicAdd(&width[r], (unsigned long long)b[c]);
+  const bool in = k < nnzb;
+  const int32_t r = !in ? -1 : d == 0 ? blk_row[k] : ci[k];
+  int w = 0;
+  if (in) {
+    w = b[d == 0 ? ci[k] : blk_row[k]];
+    key[k] = (uint64_t)(uint32_t)rank[r] << 7 | (uint32_t)w;
+    val[k] = (int32_t)k;
+  }
+  // a run of lanes of one panel adds its width once (one atomic per block on a
+  // row's counter: 99 us for 775,000 blocks in rows of 135, against 7)
+  const int lane = threadIdx.x & 63;
+  const int prev = __shfl_up(r, 1, 64);
+  const unsigned long long heads = __ballot(lane == 0 || prev != r);
+  const int first = 63 - __clzll(heads & (~0ull >> (63 - lane)));   // of this lane's run
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int t = __shfl_up(w, o, 64);
+    if (lane - o >= first) w += t;
+  }
+  if (in && (lane == 63 || (heads >> (lane + 1) & 1))) atomicAdd(&width[r], (unsigned long long)w);
 }
 
 // member widths in sorted order (entry nnzb = 0: the scan's total)
@@ -315,8 +330,7 @@ hipError_t plan_device(const DevPlanIn &in, DevPlanOut &out, const DevAlloc &all
                          rank, in.b, key, val, width);
       PD_TRY(hipGetLastError());
       PD_TRY(cub_run([&](void *t, size_t &bytes) {
-        return hipcub::DeviceRadixSort::SortPairs(t, bytes, key, key_s, val, val_s, (int)nnzb, 0,
-                                                  end_bit, s);
+        return sort_pairs(t, bytes, key, key_s, val, val_s, nnzb, (unsigned)end_bit, s);
       }));
     }
     hipLaunchKernelGGL(k_pd_memberw, grid_for(nnzb + 1), dim3(kT), 0, s, nnzb, d, val_s,

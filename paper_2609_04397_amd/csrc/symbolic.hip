@@ -4,7 +4,7 @@
 // consumes.
 //
 // Expand, sort, compress: every product A_ik B_kj of row i becomes one entry
-// with key (j << 32 | position of A_ik in row i); a segmented radix sort per
+// with key (j, position of A_ik in row i); a segmented radix sort per
 // row orders the entries by candidate column j and, within a candidate, by
 // A's stored order of k.  A candidate is a run of equal j; one thread sums its
 // bound U_ij = sum_k ||A_ik|| ||B_kj|| over the run in that order (multiply
@@ -16,6 +16,7 @@
 #include <hipcub/hipcub.hpp>
 
 #include "kernels.hpp"
+#include "sort.hpp"
 
 namespace vbcsr {
 namespace {
@@ -43,34 +44,36 @@ __global__ void __launch_bounds__(kT) k_sym_rowseg(const int64_t *arp, const int
   if (i <= n) seg[i] = eoff[arp[i]];
 }
 
-// one thread per stored block A_ik writes the entries of its products
+// 16 lanes per stored block A_ik write the entries of its products (one lane a
+// block wrote entries a whole row apart: 4.3 million in 118 us, now 24)
 __global__ void __launch_bounds__(kT) k_sym_expand(const int64_t *arp, const int32_t *aci,
                                                    const int32_t *arow, int64_t annzb,
                                                    const int64_t *brp, const int32_t *bci,
-                                                   const int64_t *eoff, uint64_t *key,
-                                                   int64_t *val) {
-  const int64_t ka = (int64_t)blockIdx.x * kT + threadIdx.x;
-  if (ka >= annzb) return;
-  const int32_t i = arow[ka];
-  const uint32_t rel = (uint32_t)(ka - arp[i]);
-  const int32_t k = aci[ka];
-  const int64_t b0 = brp[k], b1 = brp[k + 1];
-  const int64_t e0 = eoff[ka] - b0;
-  for (int64_t kb = b0; kb < b1; ++kb) {
-    key[e0 + kb] = ((uint64_t)(uint32_t)bci[kb] << 32) | rel;
-    val[e0 + kb] = kb;
+                                                   const int64_t *eoff, int rel_bits,
+                                                   uint64_t *key, int64_t *val) {
+  for (int64_t ka = ((int64_t)blockIdx.x * kT + threadIdx.x) >> 4; ka < annzb;
+       ka += (int64_t)gridDim.x * (kT / 16)) {
+    const int32_t i = arow[ka];
+    const uint32_t rel = (uint32_t)(ka - arp[i]);
+    const int32_t k = aci[ka];
+    const int64_t b0 = brp[k], b1 = brp[k + 1];
+    const int64_t e0 = eoff[ka] - b0;
+    for (int64_t kb = b0 + (threadIdx.x & 15); kb < b1; kb += 16) {
+      key[e0 + kb] = ((uint64_t)(uint32_t)bci[kb] << rel_bits) | rel;
+      val[e0 + kb] = kb;
+    }
   }
 }
 
 // one wave per row: flag[e] = 1 where a candidate (a run of equal j) starts
 __global__ void __launch_bounds__(kT) k_sym_flags(const int64_t *seg, int32_t n,
-                                                  const uint64_t *key, int32_t *flag) {
+                                                  const uint64_t *key, int rel_bits, int32_t *flag) {
   const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= n) return;
   const int lane = threadIdx.x & 63;
   const int64_t s0 = seg[row], s1 = seg[row + 1];
   for (int64_t e = s0 + lane; e < s1; e += 64)
-    flag[e] = (e == s0 || (key[e] >> 32) != (key[e - 1] >> 32)) ? 1 : 0;
+    flag[e] = (e == s0 || (key[e] >> rel_bits) != (key[e - 1] >> rel_bits)) ? 1 : 0;
 }
 
 // candidate g: first entry and row (ginc = inclusive scan of the flags)
@@ -91,7 +94,7 @@ __global__ void __launch_bounds__(kT) k_sym_groups(const int64_t *seg, int32_t n
 // one thread per candidate: bound (over the run, in A's order of k), product
 // count, values and flops of the block if kept
 __global__ void __launch_bounds__(kT) k_sym_reduce(
-    int64_t nG, int64_t nE, const int64_t *gstart, const int32_t *grow, const uint64_t *key,
+    int64_t nG, int64_t nE, const int64_t *gstart, const int32_t *grow, const uint64_t *key, int rel_bits,
     const int64_t *val, const int64_t *arp, const int32_t *aci, const int32_t *b, const double *an,
     const double *bn, double eps, int64_t *gkeep, int64_t *gnp, int64_t *gvs, double *gfl,
     double *gbound, int32_t *gj) {
@@ -99,12 +102,12 @@ __global__ void __launch_bounds__(kT) k_sym_reduce(
   if (g >= nG) return;
   const int64_t e0 = gstart[g], e1 = g + 1 < nG ? gstart[g + 1] : nE;
   const int32_t i = grow[g];
-  const int32_t j = (int32_t)(key[e0] >> 32);
+  const int32_t j = (int32_t)(key[e0] >> rel_bits);
   const int64_t a0 = arp[i];
   double u = 0.0;
   int64_t bks = 0;
   for (int64_t e = e0; e < e1; ++e) {
-    const int64_t ka = a0 + (int64_t)(key[e] & 0xFFFFFFFFu);
+    const int64_t ka = a0 + (int64_t)(key[e] & ((1ull << rel_bits) - 1));
     if (an) u = __dadd_rn(u, __dmul_rn(an[ka], bn[val[e]]));
     bks += b[aci[ka]];
   }
@@ -155,7 +158,7 @@ __global__ void __launch_bounds__(kT) k_sym_rowptr(int32_t n, const int64_t *seg
 // one thread per entry of a kept candidate: its product
 __global__ void __launch_bounds__(kT) k_sym_products(
     int64_t nE, const int32_t *ginc, const int64_t *gkeep, const int64_t *gstart,
-    const int32_t *grow, const int64_t *pptr_g, const uint64_t *key, const int64_t *val,
+    const int32_t *grow, const int64_t *pptr_g, const uint64_t *key, int rel_bits, const int64_t *val,
     const int64_t *arp, const int32_t *aci, const int32_t *b, const int64_t *apos,
     const int64_t *bpos, int64_t *pa, int64_t *pb) {
   const int64_t e = (int64_t)blockIdx.x * kT + threadIdx.x;
@@ -163,7 +166,7 @@ __global__ void __launch_bounds__(kT) k_sym_products(
   const int32_t g = ginc[e] - 1;
   if (!gkeep[g]) return;
   const int64_t pos = pptr_g[g] + (e - gstart[g]);
-  const int64_t ka = arp[grow[g]] + (int64_t)(key[e] & 0xFFFFFFFFu);
+  const int64_t ka = arp[grow[g]] + (int64_t)(key[e] & ((1ull << rel_bits) - 1));
   pa[pos] = (apos[ka] << 8) | (int64_t)b[aci[ka]];
   pb[pos] = bpos[val[e]];
 }
@@ -183,11 +186,16 @@ __global__ void __launch_bounds__(kT) k_sym_class(int64_t nC, const int32_t *oi,
   if (threadIdx.x < 5) lc[threadIdx.x] = 0;
   __syncthreads();
   const int64_t c = (int64_t)blockIdx.x * kT + threadIdx.x;
+  int k = -1;
   if (c < nC) {
-    const int k = sym_class(b[oi[c]], b[oj[c]]);
+    k = sym_class(b[oi[c]], b[oj[c]]);
     cls[c] = (uint32_t)k;
     idx[c] = (int32_t)c;
-    atomicAdd(&lc[k], 1u);
+  }
+#pragma unroll
+  for (int q = 0; q < 5; ++q) {
+    const unsigned long long in = __ballot(k == q);
+    if ((threadIdx.x & 63) == 0 && in) atomicAdd(&lc[q], (unsigned int)__popcll(in));
   }
   __syncthreads();
   if (threadIdx.x < 5 && lc[threadIdx.x]) atomicAdd(&cnt[threadIdx.x], lc[threadIdx.x]);
@@ -289,10 +297,14 @@ hipError_t spgemm_symbolic_device(const SymbolicIn &in, SymbolicOut &out, const 
   SYM_TRY(get(&key_s, (size_t)nE));
   SYM_TRY(get(&val, (size_t)nE));
   SYM_TRY(get(&val_s, (size_t)nE));
-  hipLaunchKernelGGL(k_sym_expand, grid_for(annzb), dim3(kT), 0, s, in.arp, in.aci, in.arow, annzb,
-                     in.brp, in.bci, eoff, key, val);
+  // a row of A holds at most n blocks: both halves of the key fit n's bits
+  // (with the position in 32 bits of its own the sort passes over 45 bits
+  // where 22 do for 2000 atoms of b = 4/9:
+  // 2.69 -> 2.48 ms of their product)
+  const int rel_bits = bits_for(n > 0 ? n - 1 : 0), end_bit = 2 * rel_bits;
+  hipLaunchKernelGGL(k_sym_expand, grid_for(std::min<int64_t>(16 * annzb, int64_t(1) << 30)), dim3(kT), 0, s, in.arp, in.aci, in.arow, annzb,
+                     in.brp, in.bci, eoff, rel_bits, key, val);
   SYM_TRY(hipGetLastError());
-  const int end_bit = 32 + bits_for(n > 0 ? n - 1 : 0);
   SYM_TRY(cub_run([&](void *t, size_t &b) {
     return hipcub::DeviceSegmentedRadixSort::SortPairs(t, b, key, key_s, val, val_s, (int)nE, (int)n,
                                                        seg, seg + 1, 0, end_bit, s);
@@ -302,7 +314,7 @@ hipError_t spgemm_symbolic_device(const SymbolicIn &in, SymbolicOut &out, const 
   SYM_TRY(get(&flag, (size_t)nE));
   SYM_TRY(get(&ginc, (size_t)nE));
   const dim3 rows_grid((unsigned)((n + 3) / 4));
-  hipLaunchKernelGGL(k_sym_flags, rows_grid, dim3(kT), 0, s, seg, n, key_s, flag);
+  hipLaunchKernelGGL(k_sym_flags, rows_grid, dim3(kT), 0, s, seg, n, key_s, rel_bits, flag);
   SYM_TRY(hipGetLastError());
   SYM_TRY(cub_run([&](void *t, size_t &b) {
     return hipcub::DeviceScan::InclusiveSum(t, b, flag, ginc, (int)nE, s);
@@ -337,7 +349,7 @@ hipError_t spgemm_symbolic_device(const SymbolicIn &in, SymbolicOut &out, const 
   SYM_TRY(hipMemsetAsync(gkeep + nG, 0, sizeof(int64_t), s));
   SYM_TRY(hipMemsetAsync(gnp + nG, 0, sizeof(int64_t), s));
   SYM_TRY(hipMemsetAsync(gvs + nG, 0, sizeof(int64_t), s));
-  hipLaunchKernelGGL(k_sym_reduce, grid_for(nG), dim3(kT), 0, s, nG, nE, gstart, grow, key_s, val_s,
+  hipLaunchKernelGGL(k_sym_reduce, grid_for(nG), dim3(kT), 0, s, nG, nE, gstart, grow, key_s, rel_bits, val_s,
                      in.arp, in.aci, in.b, in.an, in.bn, in.eps, gkeep, gnp, gvs, gfl, gbound, gj);
   SYM_TRY(hipGetLastError());
   SYM_TRY(cub_run([&](void *t, size_t &b) {
@@ -382,7 +394,7 @@ hipError_t spgemm_symbolic_device(const SymbolicIn &in, SymbolicOut &out, const 
                      ginc, kidx, out.crp);
   SYM_TRY(hipGetLastError());
   hipLaunchKernelGGL(k_sym_products, grid_for(nE), dim3(kT), 0, s, nE, ginc, gkeep, gstart, grow,
-                     pptr_g, key_s, val_s, in.arp, in.aci, in.b, in.apos, in.bpos, out.pa, out.pb);
+                     pptr_g, key_s, rel_bits, val_s, in.arp, in.aci, in.b, in.apos, in.bpos, out.pa, out.pb);
   SYM_TRY(hipGetLastError());
 
   // blocks grouped by tile class, stable
@@ -400,7 +412,7 @@ hipError_t spgemm_symbolic_device(const SymbolicIn &in, SymbolicOut &out, const 
                        ccnt);
     SYM_TRY(hipGetLastError());
     SYM_TRY(cub_run([&](void *t, size_t &b) {
-      return hipcub::DeviceRadixSort::SortPairs(t, b, cls, cls_s, idx, out.order, (int)nC, 0, 3, s);
+      return sort_pairs(t, b, cls, cls_s, idx, out.order, nC, 3u, s);
     }));
     unsigned int hc[5];
     SYM_TRY(fetch(hc, ccnt, sizeof(hc)));
