@@ -1075,7 +1075,7 @@ def traffic_record(kernel, workload):
 def kernel_source_sha():
     import hashlib
     h = hashlib.sha256()
-    for f in ("kernels.hip", "kernels.hpp", "abi.cpp", "planner.cpp", "common.hpp"):
+    for f in ("kernels.hip", "device.hpp", "kernels.hpp", "abi.cpp", "planner.cpp", "common.hpp"):
         h.update(open(os.path.join(ROOT, "paper_2609_04397_amd", "csrc", f), "rb").read())
     return h.hexdigest()[:16]
 

@@ -13,7 +13,8 @@
 //  * matrix cores (many right-hand sides): the panel is the A operand of
 //    16x16x4 FP64/FP32 MFMA (M = panel rows padded to 16 in registers only,
 //    K = panel columns, N = 16 right-hand sides per tile); its 4-column slices
-//    are again contiguous in memory.  The BF16x3 form uses 16x16x32 BF16 MFMA
+//    are again contiguous in memory.  FP64 products of few right-hand sides or
+//    much row padding use 4x4x4 tiles.  The BF16x3 form uses 16x16x32 BF16 MFMA
 //    on pages stored in 8-column groups (8 consecutive columns of one panel
 //    row are 16 contiguous bytes, the per-lane A fragment).
 //
@@ -1742,7 +1743,8 @@ __global__ void __launch_bounds__(kThreads) k_sddmm_mfma(SddmmParams<T> P) {
 // load instruction, EPL elements (16 bytes) per lane -- instead of 16 rows
 // per instruction, written to a wave-private LDS tile (rows padded by EPL
 // elements, so the fragment reads of the 16 rows hit distinct banks) and read
-// back in the MFMA fragment order.  X is addressed through one buffer
+// back in the MFMA fragment order.  For more than 64 right-hand sides, in
+// passes.  X is addressed through one buffer
 // descriptor (all of X within 2^31 bytes): reads past its end return zero.
 template <typename T, int CW>
 __global__ void __launch_bounds__(kThreads) k_sddmm_lds(SddmmParams<T> P) {
@@ -2046,7 +2048,9 @@ __device__ __forceinline__ void sddmm_panel(const SddmmParams<T> &P, const RowDe
   // number of stores behind the rows' loads is known, and the wait for the
   // rows leaves them in flight.
   L16 bv[NIT];
-  auto fragments = [&] {
+  auto fragments = [&](auto behind) {   // stores issued since the rows' loads
+    // vmcnt(behind): the rows are in LDS; expcnt, lgkmcnt unchanged
+    __builtin_amdgcn_s_waitcnt(0x0F70 | decltype(behind)::value);
 #pragma unroll
     for (int h = 0; h < NIT; ++h)
       bv[h] = *reinterpret_cast<const L16 *>(xm + EPL * ((kq + 4 * h) ^ perm(m)));
@@ -2058,7 +2062,7 @@ __device__ __forceinline__ void sddmm_panel(const SddmmParams<T> &P, const RowDe
   int32_t xl = rows_of(1);
   v2u32 gl = gmap_of(1);
   issue(0, 0, xn);
-  fragments();
+  fragments(std::integral_constant<int, 0>{});
   for (int j = 0; j < nt; ++j) {
     V acc0 = V{}, acc1 = V{};
 #pragma unroll
@@ -2090,8 +2094,11 @@ __device__ __forceinline__ void sddmm_panel(const SddmmParams<T> &P, const RowDe
 #pragma unroll
         for (int i = 0; i < 4; ++i) acc0[i] += acc1[i];
         out(j, acc0, gc, gx);
+        // NS stores, four without staging, any number by 64-bit addresses
+        fragments(std::integral_constant<int, (NS > 0 ? NS : NS == 0 ? 4 : 0)>{});
+      } else {
+        fragments(std::integral_constant<int, 0>{});
       }
-      fragments();
     }
   }
   if constexpr (!PAGE && NS > 0)

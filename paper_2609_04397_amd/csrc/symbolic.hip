@@ -302,7 +302,8 @@ hipError_t spgemm_symbolic_device(const SymbolicIn &in, SymbolicOut &out, const 
   // where 22 do for 2000 atoms of b = 4/9:
   // 2.69 -> 2.48 ms of their product)
   const int rel_bits = bits_for(n > 0 ? n - 1 : 0), end_bit = 2 * rel_bits;
-  hipLaunchKernelGGL(k_sym_expand, grid_for(std::min<int64_t>(16 * annzb, int64_t(1) << 30)), dim3(kT), 0, s, in.arp, in.aci, in.arow, annzb,
+  const int64_t lanes = std::min<int64_t>(16 * annzb, int64_t(1) << 30);
+  hipLaunchKernelGGL(k_sym_expand, grid_for(lanes), dim3(kT), 0, s, in.arp, in.aci, in.arow, annzb,
                      in.brp, in.bci, eoff, rel_bits, key, val);
   SYM_TRY(hipGetLastError());
   SYM_TRY(cub_run([&](void *t, size_t &b) {
