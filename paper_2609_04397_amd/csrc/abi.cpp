@@ -395,12 +395,10 @@ Route route(const vbcsr_mat *A, int d, int32_t nrhs) {
         (nrhs >= 17 && nrhs <= 32 && pad > 1.25) || (nrhs == 2 && pad > 1.75))
       return {Kind::Small, 0};
   }
-  // FP32: 5 to 8 right-hand sides are faster on 16-wide tiles than in the
-  // vector kernel's passes of 8 (particle 6: 157 against 138 us, 100,000
-  // atoms of b = 1/4/9 6: 198 against 139, 8: 173 against 141; lattice 8: 118
-  // against 109), up to 4 are not (particle 4: 121 against 131)
-  const int32_t vec_max = A->prec == VBCSR_FP32 && A->opts.nrhs_tile == 0 ? 4 : 8;
-  bool vec = path == VBCSR_PATH_VEC || (path == VBCSR_PATH_AUTO && nrhs <= vec_max);
+  // FP32 stays on the vector kernel up to 8 right-hand sides: 16-wide tiles are
+  // faster at 5 to 8 (100,000 atoms of b = 1/4/9, 8: 173 against 141 us), but
+  // their longer sums double the rounding error (2.8e-7 against 1.5e-7)
+  const bool vec = path == VBCSR_PATH_VEC || (path == VBCSR_PATH_AUTO && nrhs <= 8);
   if (vec) {
     int t = A->opts.nrhs_tile;
     if (t != 1 && t != 2 && t != 4 && t != 8) t = nrhs <= 1 ? 1 : nrhs <= 2 ? 2 : nrhs <= 4 ? 4 : 8;
