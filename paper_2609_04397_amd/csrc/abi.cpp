@@ -425,6 +425,7 @@ int product(const vbcsr_mat *A, int d, const void *X, int64_t ldx, const void *Y
     p.X = static_cast<const double *>(X);
     p.ldx = ldx;
     p.xrows = in_rows(A, d);
+    p.bmax = A->bmax;
     p.Yin = static_cast<const double *>(Yin);
     p.ldyin = ldyin;
     p.Yout = static_cast<double *>(Yout);
@@ -448,6 +449,7 @@ int product(const vbcsr_mat *A, int d, const void *X, int64_t ldx, const void *Y
     p.X = static_cast<const float *>(X);
     p.ldx = ldx;
     p.xrows = in_rows(A, d);
+    p.bmax = A->bmax;
     p.Yin = static_cast<const float *>(Yin);
     p.ldyin = ldyin;
     p.Yout = static_cast<float *>(Yout);

@@ -606,12 +606,42 @@ __device__ __forceinline__ void small_rows(const FwdParams<T> &P, const RowDesc 
       }
     }
   };
-  auto mma = [&](const double (&av)[RG], const double (&xv)[NG]) {
+  auto mma = [&](const double (&av)[RG], const double (&xv)[NG], double (&sum)[RG][NG]) {
 #pragma unroll
     for (int g = 0; g < RG; ++g)
 #pragma unroll
       for (int t = 0; t < NG; ++t)
-        acc[g][t] = __builtin_amdgcn_mfma_f64_4x4x4f64(av[g], xv[t], acc[g][t], 0, 0, 0);
+        sum[g][t] = __builtin_amdgcn_mfma_f64_4x4x4f64(av[g], xv[t], sum[g][t], 0, 0, 0);
+  };
+  // Up to 8 right-hand sides: the R steps of one turn of the ring are summed
+  // from zero and added to the total once, 4 R terms at a time.  The vector
+  // kernel splits a row over up to 128 lanes; with one chain per block the
+  // rounding error was up to 1.76 times its (relative, b = 8: 3.8e-16 against
+  // 2.2e-16 at 3 right-hand sides, now 1.8e-16; 3.8e-16 against 2.8e-16 at 8,
+  // now 1.9e-16).
+  constexpr bool kParts = NG <= 2;
+  double part[kParts ? RG : 1][kParts ? NG : 1];
+  auto begin_part = [&] {
+    if constexpr (kParts) {
+#pragma unroll
+      for (int g = 0; g < RG; ++g)
+#pragma unroll
+        for (int t = 0; t < NG; ++t) part[g][t] = 0.0;
+    }
+  };
+  auto add = [&](const double (&av)[RG], const double (&xv)[NG]) {
+    if constexpr (kParts)
+      mma(av, xv, part);
+    else
+      mma(av, xv, acc);
+  };
+  auto end_part = [&] {
+    if constexpr (kParts) {
+#pragma unroll
+      for (int g = 0; g < RG; ++g)
+#pragma unroll
+        for (int t = 0; t < NG; ++t) acc[g][t] += part[g][t];
+    }
   };
   const int ns = (K + 15) >> 4;
   double av[R][RG], xv[R][NG];
@@ -627,6 +657,7 @@ __device__ __forceinline__ void small_rows(const FwdParams<T> &P, const RowDesc 
   __builtin_amdgcn_sched_barrier(0);
   int s = 0;
   for (; s + R <= ns; s += R) {
+    begin_part();
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       const int q = (r + R - 1) % R;
@@ -634,13 +665,16 @@ __device__ __forceinline__ void small_rows(const FwdParams<T> &P, const RowDesc 
       ld_val(s + r + R - 1, av[q]);
       xi[q] = ld_idx(s + r + 2 * R - 1);
       __builtin_amdgcn_sched_barrier(0);
-      mma(av[r], xv[r]);
+      add(av[r], xv[r]);
       __builtin_amdgcn_sched_barrier(0);
     }
+    end_part();
   }
+  begin_part();
 #pragma unroll
   for (int r = 0; r + 1 < R; ++r)
-    if (s + r < ns) mma(av[r], xv[r]);
+    if (s + r < ns) add(av[r], xv[r]);
+  end_part();
   // sum over the four blocks; then, four row groups at a time, lane
   // 16 i + 4 g + j writes the row that row group g holds at i, right-hand
   // sides j of each tile
@@ -707,11 +741,11 @@ __device__ __forceinline__ void small_rows(const FwdParams<T> &P, const RowDesc 
   }
 }
 
-// NG groups of 4 right-hand sides per pass; LW right-hand sides per X load.
-template <int NG, int LW, bool MOM, int R>
+// NG groups of 4 right-hand sides and MR panel rows per pass; LW right-hand
+// sides per X load.
+template <int NG, int LW, bool MOM, int R, int MR>
 __global__ void __launch_bounds__(kThreads) k_spmm_small(FwdParams<double> P) {
   extern __shared__ double s_mom[];
-  constexpr int MR = NG <= 4 ? 32 : 16;   // panel rows per pass
   const int wg = xcd_remap(blockIdx.x, gridDim.x);
   const int row = wg * kWaves + wave_id();
   mom_init<MOM>(s_mom, P.nrhs);
@@ -2272,12 +2306,12 @@ hipError_t launch_bf16_nt(const FwdParams<float> &p, hipStream_t s, dim3 grid, s
   return hipGetLastError();
 }
 
-template <int NG, int LW, int R>
+template <int NG, int LW, int R, int MR>
 hipError_t launch_small_nr(const FwdParams<double> &p, hipStream_t s, dim3 grid, size_t shm) {
   if (p.mom)
-    hipLaunchKernelGGL((k_spmm_small<NG, LW, true, R>), grid, dim3(kThreads), shm, s, p);
+    hipLaunchKernelGGL((k_spmm_small<NG, LW, true, R, MR>), grid, dim3(kThreads), shm, s, p);
   else
-    hipLaunchKernelGGL((k_spmm_small<NG, LW, false, R>), grid, dim3(kThreads), 0, s, p);
+    hipLaunchKernelGGL((k_spmm_small<NG, LW, false, R, MR>), grid, dim3(kThreads), 0, s, p);
   return hipGetLastError();
 }
 
@@ -2287,10 +2321,18 @@ hipError_t launch_small(const FwdParams<double> &p0, hipStream_t s, dim3 grid, s
   // registers allow deeper rings only where a step is narrow: R = 3 against 2
   // is 4 % better on b = 8 at 3 right-hand sides and 14 % worse on b = 1/4/9
   // at 16
-  if (p.nrhs <= 4) return launch_small_nr<1, 1, 3>(p, s, grid, shm);
-  if (p.nrhs <= 8) return launch_small_nr<2, 2, 2>(p, s, grid, shm);
-  if (p.nrhs <= 16) return launch_small_nr<4, 2, 2>(p, s, grid, shm);
-  return launch_small_nr<8, 2, 2>(p, s, grid, shm);
+  if (p.nrhs <= 8) {
+    // operators without a block above 16: the form for 16 rows a pass, whose
+    // registers leave room for 5 waves a SIMD instead of 3 (b = 1/4/9, nrhs 4:
+    // 76 us with 32 rows a pass, 72 with 16; b = 5 54 and 46, b = 1 74 and 49)
+    if (p.bmax <= 16)
+      return p.nrhs <= 4 ? launch_small_nr<1, 1, 3, 16>(p, s, grid, shm)
+                         : launch_small_nr<2, 2, 2, 16>(p, s, grid, shm);
+    return p.nrhs <= 4 ? launch_small_nr<1, 1, 3, 32>(p, s, grid, shm)
+                       : launch_small_nr<2, 2, 2, 32>(p, s, grid, shm);
+  }
+  if (p.nrhs <= 16) return launch_small_nr<4, 2, 2, 32>(p, s, grid, shm);
+  return launch_small_nr<8, 2, 2, 16>(p, s, grid, shm);
 }
 
 template <typename T>

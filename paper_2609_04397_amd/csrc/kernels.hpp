@@ -31,6 +31,7 @@ struct FwdParams {
   int64_t xrows;        // rows of X (columns of the operator)
   int32_t xrow16;       // set by the launcher: X rows start on 16-byte boundaries
   int32_t yrow16;       // set by the launcher: so do the rows the epilogue touches
+  int32_t bmax;         // largest block size of the operator
   const T *Yin;
   int64_t ldyin;
   T *Yout;

@@ -1,0 +1,65 @@
+"""Rounding error of the FP64 products against sums in extended precision: the
+matrix-core tiles split a row's sum at least as finely as the kernels that
+they take the place of."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import dev
+from workloads import random_cube, sc_lattice
+
+from paper_2609_04397_amd.matrix import Matrix
+
+pytestmark = pytest.mark.gpu
+
+OPS = {
+    "1_4_9": lambda: random_cube(1500, 0.1, [(1, 300), (4, 600), (9, 600)], 5.2, 2.0, seed=3),
+    "8": lambda: random_cube(1200, 0.1, [(8, 1200)], 5.2, 2.0, seed=4),
+    "13": lambda: sc_lattice(10, 13, seed=5),
+}
+
+
+def row_sums(op, transpose, values, X):
+    """op(A) X in the precision of the arguments, from scalar entries."""
+    b = op.b.astype(np.int64)
+    off = np.concatenate([[0], np.cumsum(b)])
+    rows = np.repeat(np.arange(b.size), np.diff(op.row_ptr))
+    size = b[rows] * b[op.col_idx]
+    blk = np.repeat(np.arange(rows.size), size)
+    loc = np.arange(size.sum()) - (np.cumsum(size) - size)[blk]
+    bj = b[op.col_idx][blk]
+    r, c = off[rows[blk]] + loc // bj, off[op.col_idx[blk]] + loc % bj
+    if transpose:
+        r, c = c, r
+    o = np.argsort(r, kind="stable")
+    r = r[o]
+    first = np.flatnonzero(np.concatenate([[True], r[1:] != r[:-1]]))
+    Y = np.zeros((off[-1], X.shape[1]), X.dtype)
+    Y[r[first]] = np.add.reduceat(values[o][:, None] * X[c[o]], first, axis=0)
+    return Y
+
+
+def rel(y, ref):
+    d = y - ref
+    return float(np.sqrt((np.abs(d) ** 2).sum() / (np.abs(ref) ** 2).sum()))
+
+
+# About 10^4 output rows times up to 4 columns are compared, so that the two
+# root-mean-square errors are known to about 1 %: 10 % is well outside of it.
+@pytest.mark.parametrize("transpose", [False, True])
+@pytest.mark.parametrize("name", list(OPS))
+def test_few_right_hand_sides_sum_like_the_vector_kernel(name, transpose):
+    op = OPS[name]()
+    rng = np.random.default_rng(7)
+    N = int(op.b.sum())
+    v = rng.uniform(-1, 1, op.values.size)
+    X = rng.standard_normal((N, 8))
+    ref = row_sums(op, transpose, v.astype(np.longdouble), X[:, :4].astype(np.longdouble))
+    A = Matrix.from_operator(op, values=v)
+    B = Matrix.from_operator(op, values=v, path="vec")
+    for n in (2, 3, 4, 5, 8):
+        k = min(n, 4)
+        Xd = dev(X[:, :n], "fp64")
+        ea, eb = (rel(M.spmm(Xd, transpose=transpose).cpu().numpy()[:, :k], ref[:, :k])
+                  for M in (A, B))
+        assert ea <= 1.1 * eb, (n, ea, eb)
