@@ -248,6 +248,7 @@ struct DevDir {
   int64_t n_values = 0, n_values16 = 0;
   int32_t npanels = 0;        // forward: block rows; transposed: block columns
   double pad16 = 1.0;         // panel rows in tiles of 16 over those in tiles of 4
+  double height = 1.0;        // mean panel height, each panel by its rows
 };
 
 int env_path() {
@@ -380,20 +381,28 @@ Route route(const vbcsr_mat *A, int d, int32_t nrhs) {
   int path = env_path();
   if (path == VBCSR_PATH_AUTO) path = A->opts.path;
   if (A->prec == VBCSR_BF16X3) return {Kind::Bf16x3, nrhs <= 16 ? 1 : nrhs <= 32 ? 2 : 4};
-  // FP64 small tiles where the path is left open: 3 to 8 right-hand sides on
-  // any operator (from level, b = 13 at 4, to 34 % faster, b = 1/4/9 at 8); 9
-  // to 16 unless 16-row tiles pad nothing (b = 13: 217 us against 227 at 16;
-  // b = 13/9/1, ratio 1.14: 276 against 263 at 12; b = 9..20, ratio 1.33: 177
-  // against 141 at 16); 17 to 32 where they pad more (b = 13/9/1 309 against
-  // 318 at 20; b = 9..20 240 against 218 at 32; b = 1/4/9 197 against 178 at
-  // 24); 2 where they pad to twice the rows (b = 8: 112 against 105 us, b =
-  // 1/4/9 98 against 89; b = 9..20 98 against 104, b = 13/9/1 179 against
-  // 200); 1 nowhere.
+  // FP64 small tiles where the path is left open, by the mean panel height h
+  // (each panel by its rows) and the padding ratio of 16-row tiles; us on the
+  // kernel that it keeps out and on small tiles:
+  //   2 right-hand sides: h <= 6 (b = 5: 59 against 44, b = 6: 119/117, b = 7:
+  //     107/111, b = 1/4/9, h = 7.2: 64/69, b = 8: 88/95);
+  //   3 and 4: h <= 20 (b = 8: 105/98, b = 9..20: 91/86, b = 24: 102/105,
+  //     b = 28: 113/124, b = 40: 143/182);
+  //   5 to 8: every operator (b = 13 at 8: 217/195, b = 1/4/9: 100/82);
+  //   9 to 16: unless 16-row tiles pad nothing (b = 13: 217/227 at 16; b =
+  //     13/9/1, ratio 1.14: 276/263 at 12; b = 9..20, ratio 1.33: 177/141);
+  //   17 to 32: where they pad more (b = 13/9/1 309/318 at 20; b = 9..20
+  //     240/218 at 32; b = 1/4/9 197/178 at 24).
   if (A->prec == VBCSR_FP64 && path == VBCSR_PATH_AUTO && A->opts.nrhs_tile == 0) {
-    const double pad = A->dir[d].pad16;
-    if ((nrhs >= 3 && nrhs <= 8) || (nrhs >= 9 && nrhs <= 16 && pad > 1.05) ||
-        (nrhs >= 17 && nrhs <= 32 && pad > 1.25) || (nrhs == 2 && pad > 1.75))
-      return {Kind::Small, 0};
+    const double pad = A->dir[d].pad16, h = A->dir[d].height;
+    const bool small = nrhs <= 1    ? false
+                       : nrhs == 2  ? h <= 6.0
+                       : nrhs <= 4  ? h <= 20.0
+                       : nrhs <= 8  ? true
+                       : nrhs <= 16 ? pad > 1.05
+                       : nrhs <= 32 ? pad > 1.25
+                                    : false;
+    if (small) return {Kind::Small, 0};
   }
   // FP32 stays on the vector kernel up to 8 right-hand sides: 16-wide tiles are
   // faster at 5 to 8 (100,000 atoms of b = 1/4/9, 8: 173 against 141 us), but
@@ -585,6 +594,7 @@ int create_impl(vbcsr_mat **out, int32_t n_atoms, const int32_t *block_sizes,
     D.n_values16 = P.n_values16;
     D.npanels = (int32_t)P.rows.size();
     D.pad16 = pad_ratio(block_sizes, block_sizes + P.rows.size());
+    D.height = mean_height(block_sizes, block_sizes + P.rows.size());
     if ((rc = upload_into(A, &D.rows, P.rows, s))) return bail(rc);
     if ((rc = upload_into(A, &D.blk_pos, P.blk_pos, s))) return bail(rc);
     if ((rc = upload_into(A, &D.blk_k0, P.blk_k0, s))) return bail(rc);
@@ -700,6 +710,7 @@ int create_planned_on_device(vbcsr_mat **out, const vbcsr_mat *A, int64_t nnzb, 
     D.n_values16 = 0;
     D.npanels = n;
     D.pad16 = A->dir[d].pad16;
+    D.height = A->dir[d].height;
     if ((rc = finish_direction(C, d, po.dir[d].n_cols, s))) return rc;
   }
   if (C->nnz > 0 && d_vals && (rc = pack_all(C, d_vals, 0, s))) return rc;

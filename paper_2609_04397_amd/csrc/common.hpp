@@ -167,4 +167,15 @@ double pad_ratio(It first, It last) {
   return r4 ? (double)r16 / (double)r4 : 1.0;
 }
 
+// Mean of these panel heights, each panel counted by its rows.
+template <typename It>
+double mean_height(It first, It last) {
+  int64_t rows = 0, sq = 0;
+  for (; first != last; ++first) {
+    rows += *first;
+    sq += (int64_t)*first * *first;
+  }
+  return rows ? (double)sq / (double)rows : 1.0;
+}
+
 }  // namespace vbcsr

@@ -14,6 +14,8 @@ pytestmark = pytest.mark.gpu
 
 OPS = {
     "1_4_9": lambda: random_cube(1500, 0.1, [(1, 300), (4, 600), (9, 600)], 5.2, 2.0, seed=3),
+    "5": lambda: random_cube(2000, 0.1, [(5, 2000)], 5.2, 2.0, seed=8),
+    "28": lambda: random_cube(400, 0.1, [(28, 400)], 5.2, 2.0, seed=9),
     "8": lambda: random_cube(1200, 0.1, [(8, 1200)], 5.2, 2.0, seed=4),
     "13": lambda: sc_lattice(10, 13, seed=5),
 }
