@@ -233,14 +233,19 @@ __device__ __forceinline__ void zstore(const ZSpmmParams<T> &P, int64_t r, int c
 // or right-hand side i of a group (X); one load brings one complex value.
 // Four real products per complex one go to two accumulators (the imaginary
 // part of the value enters the real one negated); FP32 pages and vectors are
-// widened on load and accumulate in FP64.  A ring of R register sets: the
+// widened on load and accumulate in FP64.  PARTS (FP64 below 16 right-hand
+// sides): each step is summed from zero and added to the total once.  With one
+// chain per block the rounding error was 1.4 times that of the vector kernel,
+// which splits a row over up to 64 lanes (b = 1/4/9: 4.4e-16 of the result
+// against 3.2e-16, now 2.0e-16), and from 16 on it is below that of 16-row
+// tiles without (4.4e-16 against 6.2e-16).  A ring of R register sets: the
 // next R - 1 steps are in flight, their indices R further ahead; an index is
 // compared with the panel's end where it is used (at the load it would be
 // waited for).  The blocks' partial sums meet once per panel.
 // Bound by the load path (16 cycles of a compute unit per load): O(k) of the
 // b = 1/4/9 cube of 20 000 atoms, 16 right-hand sides, 98 us against 181 us
 // with 16-row tiles, whose matrix work was mostly padding; R = 3 110 us.
-template <typename T, int RG, int NG, int R>
+template <typename T, int RG, int NG, int R, bool PARTS>
 __device__ __forceinline__ void zsmall_rows(const ZSpmmParams<T> &P, const RowDesc &rd, int m0, int c0,
                                             uint32_t xbytes) {
   constexpr uint32_t ES = 2 * sizeof(T);
@@ -277,6 +282,35 @@ __device__ __forceinline__ void zsmall_rows(const ZSpmmParams<T> &P, const RowDe
     for (int g = 0; g < RG; ++g) a[g] = zload<T>(ra, vo + (uint32_t)s * vstep + 4u * ES * g);
   };
   auto mma = [&](const double2 (&a)[RG], const double2 (&x)[NG]) {
+    if constexpr (PARTS) {
+      // added one row group behind the matrix instructions that form them
+      double pr[2][NG], pi[2][NG];
+#pragma unroll
+      for (int g = 0; g <= RG; ++g) {
+        if (g < RG) {
+          const double n = -a[g % RG].y;
+#pragma unroll
+          for (int t = 0; t < NG; ++t) {
+            pr[g & 1][t] = __builtin_amdgcn_mfma_f64_4x4x4f64(a[g % RG].x, x[t].x, 0.0, 0, 0, 0);
+            pi[g & 1][t] = __builtin_amdgcn_mfma_f64_4x4x4f64(a[g % RG].x, x[t].y, 0.0, 0, 0, 0);
+          }
+#pragma unroll
+          for (int t = 0; t < NG; ++t) {
+            pr[g & 1][t] = __builtin_amdgcn_mfma_f64_4x4x4f64(n, x[t].y, pr[g & 1][t], 0, 0, 0);
+            pi[g & 1][t] = __builtin_amdgcn_mfma_f64_4x4x4f64(a[g % RG].y, x[t].x, pi[g & 1][t], 0, 0, 0);
+          }
+        }
+        if (g > 0) {
+#pragma unroll
+          for (int t = 0; t < NG; ++t) {
+            re[g - 1][t] += pr[(g - 1) & 1][t];
+            im[g - 1][t] += pi[(g - 1) & 1][t];
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      return;
+    }
 #pragma unroll
     for (int g = 0; g < RG; ++g)
 #pragma unroll
@@ -341,7 +375,7 @@ __device__ __forceinline__ void zsmall_rows(const ZSpmmParams<T> &P, const RowDe
   }
 }
 
-template <typename T, int NG, int R>
+template <typename T, int NG, int R, bool PARTS>
 __global__ void __launch_bounds__(kThreads) k_zspmm_small(ZSpmmParams<T> P, uint32_t xbytes) {
   const int row = xcd_remap(blockIdx.x, gridDim.x) * kWaves + wave_id();
   if (row >= P.nrows) return;
@@ -349,10 +383,10 @@ __global__ void __launch_bounds__(kThreads) k_zspmm_small(ZSpmmParams<T> P, uint
   for (int c0 = 0; c0 < P.nrhs; c0 += 4 * NG)
     for (int m0 = 0; m0 < rd.b; m0 += 16) {
       switch ((min(rd.b - m0, 16) + 3) >> 2) {
-        case 1: zsmall_rows<T, 1, NG, R>(P, rd, m0, c0, xbytes); break;
-        case 2: zsmall_rows<T, 2, NG, R>(P, rd, m0, c0, xbytes); break;
-        case 3: zsmall_rows<T, 3, NG, R>(P, rd, m0, c0, xbytes); break;
-        default: zsmall_rows<T, 4, NG, R>(P, rd, m0, c0, xbytes); break;
+        case 1: zsmall_rows<T, 1, NG, R, PARTS>(P, rd, m0, c0, xbytes); break;
+        case 2: zsmall_rows<T, 2, NG, R, PARTS>(P, rd, m0, c0, xbytes); break;
+        case 3: zsmall_rows<T, 3, NG, R, PARTS>(P, rd, m0, c0, xbytes); break;
+        default: zsmall_rows<T, 4, NG, R, PARTS>(P, rd, m0, c0, xbytes); break;
       }
     }
 }
@@ -361,7 +395,11 @@ __global__ void __launch_bounds__(kThreads) k_zspmm_small(ZSpmmParams<T> P, uint
 // sides: one wave per panel, M = panel rows in tiles of 16, K = panel columns
 // in slices of 4, N = 16 right-hand sides per tile, NT tiles per pass.  Lane
 // (m, kq) loads 16 bytes of A (row m, column 4s + kq: one complex value) and,
-// per tile, 16 bytes of X; accumulators, ring and padding as above.
+// per tile, 16 bytes of X; ring and padding as above.  Each of the four real
+// products has an accumulator of its own: with two, whose chains are twice as
+// long, the rounding error was 1.4 times larger (b = 9..20: 1.41e-15 against
+// 0.99e-15 of the result) at the same speed (b = 13, 32 right-hand sides 297
+// us with two, 298 with four; b = 9..20 493 and 472).
 template <int NT, int R>
 __global__ void __launch_bounds__(kThreads) k_zspmm_mfma(ZSpmmParams<double> P, uint32_t xbytes) {
   const int row = xcd_remap(blockIdx.x, gridDim.x) * kWaves + wave_id();
@@ -377,11 +415,11 @@ __global__ void __launch_bounds__(kThreads) k_zspmm_mfma(ZSpmmParams<double> P, 
   for (int mt = 0; mt * 16 < b; ++mt) {
     const uint32_t vo = (uint32_t)(kq * b + mt * 16 + m) * 16u, vstep = (uint32_t)(4 * b) * 16u;
     for (int c0 = 0; c0 < P.nrhs; c0 += 16 * NT) {
-      v4d re[NT], im[NT];
+      v4d re[NT], im[NT], ii[NT], ir[NT];
       uint32_t xcol[NT];
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
-        re[t] = im[t] = v4d{0.0, 0.0, 0.0, 0.0};
+        re[t] = im[t] = ii[t] = ir[t] = v4d{0.0, 0.0, 0.0, 0.0};
         const int c = c0 + 16 * t + m;
         xcol[t] = c < P.nrhs ? (uint32_t)c * 16u : kOutCol;
       }
@@ -395,16 +433,12 @@ __global__ void __launch_bounds__(kThreads) k_zspmm_mfma(ZSpmmParams<double> P, 
         a = zload<double>(ra, vo + (uint32_t)s * vstep);
       };
       auto mma = [&](const double2 &a, const double2 (&x)[NT]) {
-        const double n = -a.y;
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
           re[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, x[t].x, re[t], 0, 0, 0);
+          ii[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, x[t].y, ii[t], 0, 0, 0);
           im[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, x[t].y, im[t], 0, 0, 0);
-        }
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-          re[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(n, x[t].y, re[t], 0, 0, 0);
-          im[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, x[t].x, im[t], 0, 0, 0);
+          ir[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, x[t].x, ir[t], 0, 0, 0);
         }
       };
       double2 av[R], xv[R][NT];
@@ -439,7 +473,7 @@ __global__ void __launch_bounds__(kThreads) k_zspmm_mfma(ZSpmmParams<double> P, 
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const int r = mt * 16 + kq + 4 * e;
-          if (r < b && c < P.nrhs) zstore(P, (int64_t)rd.yrow + r, c, re[t][e], im[t][e]);
+          if (r < b && c < P.nrhs) zstore(P, (int64_t)rd.yrow + r, c, re[t][e] - ii[t][e], im[t][e] + ir[t][e]);
         }
       }
     }
@@ -525,16 +559,21 @@ hipError_t launch_zspmm_any(const ZSpmmParams<T> &p, hipStream_t s) {
       if (p.nrhs <= 32)
         hipLaunchKernelGGL((k_zspmm_mfma<2, 4>), grid, dim3(kThreads), 0, s, p, xb);
       else
-        hipLaunchKernelGGL((k_zspmm_mfma<4, 3>), grid, dim3(kThreads), 0, s, p, xb);
+        hipLaunchKernelGGL((k_zspmm_mfma<4, 2>), grid, dim3(kThreads), 0, s, p, xb);
       return hipGetLastError();
     }
   }
+  constexpr bool kF64 = sizeof(T) == 8;
   if (p.nrhs <= 4)
-    hipLaunchKernelGGL((k_zspmm_small<T, 1, 2>), grid, dim3(kThreads), 0, s, p, xb);
+    hipLaunchKernelGGL((k_zspmm_small<T, 1, 2, kF64>), grid, dim3(kThreads), 0, s, p, xb);
   else if (p.nrhs <= 8)
-    hipLaunchKernelGGL((k_zspmm_small<T, 2, 2>), grid, dim3(kThreads), 0, s, p, xb);
+    hipLaunchKernelGGL((k_zspmm_small<T, 2, 2, kF64>), grid, dim3(kThreads), 0, s, p, xb);
+  else if (kF64 && p.nrhs <= 12)
+    hipLaunchKernelGGL((k_zspmm_small<T, 3, 2, kF64>), grid, dim3(kThreads), 0, s, p, xb);
+  else if (kF64 && p.nrhs < 16)
+    hipLaunchKernelGGL((k_zspmm_small<T, 4, 2, kF64>), grid, dim3(kThreads), 0, s, p, xb);
   else
-    hipLaunchKernelGGL((k_zspmm_small<T, 4, 2>), grid, dim3(kThreads), 0, s, p, xb);
+    hipLaunchKernelGGL((k_zspmm_small<T, 4, 2, false>), grid, dim3(kThreads), 0, s, p, xb);
   return hipGetLastError();
 }
 
