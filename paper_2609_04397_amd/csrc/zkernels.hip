@@ -540,8 +540,8 @@ hipError_t launch_zsample(const ZSampleParams &p, void *fwd, void *tr, int elem_
 }
 
 // Matrix cores when X spans less than one buffer descriptor (kXSpan), else
-// the vector kernel with 64-bit addresses.  Small tiles for every operator up
-// to 16 right-hand sides and in FP32 (vector kernel against small tiles, FP64
+// the vector kernel with 64-bit addresses.  Small tiles for operators of any but
+// the smallest blocks up to 16 right-hand sides and in FP32 (vector kernel against small tiles, FP64
 // O(k) of the b = 1/4/9 cube of 20 000 atoms: 51 against 43 us at 1, 77/49 at
 // 4, 196/66 at 8; FP32 42/37 at 1, 99/55 at 8, 201/94 at 16, 385/180 at 32;
 // 16-row tiles against small tiles at 16: 181/98).  FP64 beyond 16: small
@@ -551,7 +551,18 @@ hipError_t launch_zsample(const ZSampleParams &p, void *fwd, void *tr, int elem_
 template <typename T>
 hipError_t launch_zspmm_any(const ZSpmmParams<T> &p, hipStream_t s) {
   const int64_t xbytes = (((int64_t)p.xrows - 1) * p.ldx + p.nrhs) * 2 * (int64_t)sizeof(T);
-  if (p.nrows == 0 || xbytes >= kXSpan) return launch_zspmm_t(p, s);
+  // The vector kernel too where a small tile of 4 rows is mostly padding (mean
+  // panel height of 2 or 3) and few right-hand sides leave it the value stream
+  // alone; us on it and on small tiles, operators of one size: FP32, 1
+  // right-hand side, b = 1 39/68, b = 3 47/60; 2, b = 1 45/67, b = 3 52/59; 4,
+  // b = 1 63/66, b = 2 59/63, b = 3 74/59; FP64, 1, b = 1 44/57, b = 3 80/83;
+  // 2, b = 2 55/62, b = 3 91/87; 4, b = 1 105/56.
+  constexpr bool kF64 = sizeof(T) == 8;
+  const double flat = p.nrhs == 1   ? 3.0
+                      : p.nrhs == 2 ? (kF64 ? 2.0 : 3.0)
+                      : p.nrhs <= 4 ? (kF64 ? 0.0 : 2.0)
+                                    : 0.0;
+  if (p.nrows == 0 || xbytes >= kXSpan || p.height <= flat) return launch_zspmm_t(p, s);
   const dim3 grid((unsigned)((p.nrows + kWaves - 1) / kWaves));
   const uint32_t xb = (uint32_t)xbytes;
   if constexpr (sizeof(T) == 8) {
@@ -563,7 +574,6 @@ hipError_t launch_zspmm_any(const ZSpmmParams<T> &p, hipStream_t s) {
       return hipGetLastError();
     }
   }
-  constexpr bool kF64 = sizeof(T) == 8;
   if (p.nrhs <= 4)
     hipLaunchKernelGGL((k_zspmm_small<T, 1, 2, kF64>), grid, dim3(kThreads), 0, s, p, xb);
   else if (p.nrhs <= 8)

@@ -58,6 +58,7 @@ struct ZSpmmParams {
   double ar, ai, br, bi;
   int64_t xrows;  // rows of X (columns of the operator)
   double pad16;   // pad_ratio of the block sizes
+  double height;  // mean_height of the block sizes
 };
 
 hipError_t launch_zphase(const ZPhaseParams &p, hipStream_t s);

@@ -21,7 +21,7 @@ struct vbcsr_zmat {
   int64_t nkb = 0, nkv = 0;           // blocks and values of O(k)
   vbcsr_prec prec = VBCSR_FP64;
   bool has_tau = false;
-  double pad16 = 1.0;
+  double pad16 = 1.0, height = 1.0;
   std::vector<int64_t> krp_host;
   std::vector<int32_t> kci_host;
   // device
@@ -228,6 +228,7 @@ int vbcsr_zmat_create(vbcsr_zmat **out, int32_t n_atoms, const int32_t *block_si
   Z->nkv = nkv;
   Z->prec = prec;
   Z->pad16 = pad_ratio(block_sizes, block_sizes + n_atoms);
+  Z->height = mean_height(block_sizes, block_sizes + n_atoms);
   Z->has_tau = tau != nullptr;
   Z->krp_host = krp;
   Z->kci_host = kci;
@@ -334,12 +335,12 @@ int vbcsr_zmat_spmm(const vbcsr_zmat *Z, const void *X, int64_t ldx, void *Y, in
   if (Z->prec == VBCSR_FP64) {
     ZSpmmParams<double> p{Z->rows[d], Z->n, Z->colx[d], static_cast<const double *>(Z->pages[d]),
                           static_cast<const double *>(X), ldx, static_cast<double *>(Y), ldy, nrhs,
-                          alpha[0], alpha[1], beta[0], beta[1], Z->N, Z->pad16};
+                          alpha[0], alpha[1], beta[0], beta[1], Z->N, Z->pad16, Z->height};
     e = launch_zspmm_f64(p, s);
   } else {
     ZSpmmParams<float> p{Z->rows[d], Z->n, Z->colx[d], static_cast<const float *>(Z->pages[d]),
                          static_cast<const float *>(X), ldx, static_cast<float *>(Y), ldy, nrhs,
-                         alpha[0], alpha[1], beta[0], beta[1], Z->N, Z->pad16};
+                         alpha[0], alpha[1], beta[0], beta[1], Z->N, Z->pad16, Z->height};
     e = launch_zspmm_f32(p, s);
   }
   if (e != hipSuccess) return zhip(e, "complex product kernel launch");
