@@ -1347,8 +1347,8 @@ int vbcsr_get_values(const vbcsr_mat *A, void *values, int dtype, void *stream) 
   if (!values) return fail(VBCSR_EINVAL, "values is NULL");
   const DevDir &D = A->dir[0];
   hipError_t e = launch_unpack(D.vals, A->prec == VBCSR_FP64 ? 8 : 4, D.blk_pos, A->blk_row,
-                               A->col_idx, A->b, A->gbase, A->nnzb, values,
-                               static_cast<hipStream_t>(stream));
+                               A->col_idx, A->b, A->gbase, A->nnzb, A->nnz, A->bmax,
+                               values, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail(e, "unpack kernel launch");
   return VBCSR_OK;
 } catch (...) {

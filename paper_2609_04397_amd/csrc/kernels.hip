@@ -1596,7 +1596,7 @@ __global__ void __launch_bounds__(kThreads) k_refresh_records(PackParams P, cons
 // at the destination; the records go through `tab` (the wave's LDS).
 template <typename T>
 __device__ __forceinline__ void transpose_run(const PageRec &r, PageRec *tab, int nb, int lane,
-                                              const T *src, T *dst) {
+                                              int part, int parts, const T *src, T *dst) {
   int n = 0;
   if (lane < nb) {
     n = r.bi * r.bj;
@@ -1614,7 +1614,7 @@ __device__ __forceinline__ void transpose_run(const PageRec &r, PageRec *tab, in
   const int len = __builtin_amdgcn_readlane(incl, nb - 1);
 #pragma unroll
   for (int u = 0; u < kPackRun; ++u) st[u] = u < nb ? __builtin_amdgcn_readlane(start, u) : len;
-  for (int e0 = lane; e0 < len; e0 += 64 * kPackChunk) {
+  for (int e0 = 64 * kPackChunk * part + lane; e0 < len; e0 += 64 * kPackChunk * parts) {
     T v[kPackChunk];
     int64_t d[kPackChunk];
 #pragma unroll
@@ -1654,7 +1654,7 @@ __global__ void __launch_bounds__(kThreads) k_refresh(const PageRec *rec, int64_
   const int nb = (int)min((int64_t)kPackRun, nnzb - u0);
   PageRec r{};
   if (lane < nb) r = rec[u0 + lane];
-  transpose_run<T>(r, tab_all + wave_id() * kPackRun, nb, lane, src, dst);
+  transpose_run<T>(r, tab_all + wave_id() * kPackRun, nb, lane, 0, 1, src, dst);
 }
 
 // ---------------------------------------------------------------------------
@@ -2592,7 +2592,7 @@ __global__ void __launch_bounds__(kThreads) k_gather_blocks(const double *src,
   for (int e = lane; e < size[t]; e += 64) dp[e] = sp[e];
 }
 
-// Forward pages -> graph order (each block row-major at gbase): a wave takes
+// Forward pages -> graph order (each block row-major at gbase): `parts` waves take
 // kPackRun blocks, whose values are one run of the destination (a million
 // blocks of 1, 4 and 9: 112 us, 374 with one block a wave; 775,000 blocks of
 // 9 to 20, 1.3 GB each way: 645 both ways, 4 TB/s, columns read 8 bytes a lane).
@@ -2600,9 +2600,11 @@ template <typename T>
 __global__ void __launch_bounds__(kThreads) k_unpack(const T *pages, const int64_t *pos,
                                                      const int32_t *blk_row,
                                                      const int32_t *col_idx, const int32_t *b,
-                                                     const int64_t *gbase, int64_t nnzb, T *dst) {
+                                                     const int64_t *gbase, int64_t nnzb, int parts, T *dst) {
   __shared__ PageRec tab_all[kWaves * kPackRun];
-  const int64_t k0 = ((int64_t)blockIdx.x * kWaves + wave_id()) * kPackRun;
+  const int64_t w = (int64_t)blockIdx.x * kWaves + wave_id();
+  const int part = (int)(w % parts);
+  const int64_t k0 = w / parts * kPackRun;
   if (k0 >= nnzb) return;
   const int lane = threadIdx.x & 63;
   const int nb = (int)min((int64_t)kPackRun, nnzb - k0);
@@ -2615,7 +2617,7 @@ __global__ void __launch_bounds__(kThreads) k_unpack(const T *pages, const int64
     r.bi = b[blk_row[k]];
     r.bj = b[col_idx[k]];
   }
-  transpose_run<T>(r, tab, nb, lane, pages, dst);
+  transpose_run<T>(r, tab, nb, lane, part, parts, pages, dst);
 }
 
 // ---------------------------------------------------------------------------
@@ -2874,17 +2876,27 @@ hipError_t launch_gather_blocks(const double *src, const int64_t *sbase, const i
 
 hipError_t launch_unpack(const void *pages, int elem_bytes, const int64_t *pos,
                          const int32_t *blk_row, const int32_t *col_idx, const int32_t *b,
-                         const int64_t *gbase, int64_t nnzb, void *dst, hipStream_t s) {
+                         const int64_t *gbase, int64_t nnzb, int64_t nnz, int bmax, void *dst,
+                         hipStream_t s) {
   if (nnzb == 0) return hipSuccess;
-  const int64_t waves = (nnzb + kPackRun - 1) / kPackRun;
+  const int64_t runs = (nnzb + kPackRun - 1) / kPackRun;
+  // Waves of a run: each about 1024 values, and where the runs are too few to
+  // fill the chip enough for 8192 waves, as long as the longest run can use
+  // them (30 atoms of b = 64: 20 us with one wave a block, 96 with one a run,
+  // now 13; 1,000 atoms of b = 1/4/9 with one of 64: 22, 27 and 18; 10,000 of
+  // b = 13: 210, 190 and 180).
+  const int64_t avg = (nnz / runs + 1023) / 1024;
+  const int64_t most = ((int64_t)kPackRun * bmax * bmax + 64 * kPackChunk - 1) / (64 * kPackChunk);
+  const int parts = (int)std::max(avg, std::min((8191 + runs) / runs, most));
+  const int64_t waves = runs * parts;
   const dim3 grid((unsigned)((waves + kWaves - 1) / kWaves));
   if (elem_bytes == 8)
     hipLaunchKernelGGL(k_unpack<double>, grid, dim3(kThreads), 0, s,
-                       static_cast<const double *>(pages), pos, blk_row, col_idx, b, gbase, nnzb,
+                       static_cast<const double *>(pages), pos, blk_row, col_idx, b, gbase, nnzb, parts,
                        static_cast<double *>(dst));
   else
     hipLaunchKernelGGL(k_unpack<float>, grid, dim3(kThreads), 0, s,
-                       static_cast<const float *>(pages), pos, blk_row, col_idx, b, gbase, nnzb,
+                       static_cast<const float *>(pages), pos, blk_row, col_idx, b, gbase, nnzb, parts,
                        static_cast<float *>(dst));
   return hipGetLastError();
 }

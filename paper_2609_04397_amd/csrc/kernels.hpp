@@ -267,7 +267,8 @@ hipError_t launch_gather_blocks(const double *src, const int64_t *sbase, const i
 // Forward pages (elem_bytes 8 or 4) -> graph-order row-major blocks at gbase.
 hipError_t launch_unpack(const void *pages, int elem_bytes, const int64_t *pos,
                          const int32_t *blk_row, const int32_t *col_idx, const int32_t *b,
-                         const int64_t *gbase, int64_t nnzb, void *dst, hipStream_t s);
+                         const int64_t *gbase, int64_t nnzb, int64_t nnz, int bmax, void *dst,
+                         hipStream_t s);
 
 // Kernel polynomial method: coef[k] = damped, doubled moments (damping 0 =
 // none, 1 = Jackson), then rho[i] = density of states at x[i] (|x| < 1).
