@@ -872,17 +872,19 @@ __global__ void __launch_bounds__(kThreads) k_spmm_mfma(FwdParams<T> P) {
         for (int t = 0; t < NT; ++t) acc[t] = V{};
         const __amdgpu_buffer_rsrc_t rv = panel_rsrc(vals, (uint32_t)((int64_t)K * b * sizeof(T)));
         const __amdgpu_buffer_rsrc_t rc = panel_rsrc(cx, (uint32_t)(K * 4));
-        // FP32: lane (m, kq) loads row m of column kq of a slice.  Rows past
-        // the panel read the next column's values into tile rows that are
-        // never stored: four neighbouring lanes of which some are out of
-        // range take the slow path of the load unit.
+        // FP32: lane (m, kq) loads row m of column kq of a slice.  Four
+        // neighbouring lanes are in range together, or they take the slow path
+        // of the load unit: rows past the panel, to the next multiple of four,
+        // read the next column's values into tile rows that are never stored.
+        // Those beyond load nothing (b = 8, nrhs 64: 167 us; reading on 178).
         // FP64: an 8-byte load costs the unit as much as one of 16, so lane
         // (m, kq) loads rows 2 (m % 8) and 2 (m % 8) + 1 of column 2 kq + m / 8
         // of the group's 8 columns in one, and lanes m and m + 8 then exchange
         // halves (fill_pair below): slice u of a group holds its columns
         // 2 kq + u, tile row m the panel row tile_row(m).
         const uint32_t vlane = PAIR ? (uint32_t)((2 * kq + (m >> 3)) * b + mt * 16 + 2 * (m & 7)) * 8u
-                                    : (uint32_t)(kq * b + p) * (uint32_t)sizeof(T);
+                               : (p & ~3) < b ? (uint32_t)(kq * b + p) * (uint32_t)sizeof(T)
+                                              : kOutRow;
         // XB: all of X lies within 2^31 bytes and is read through one buffer
         // descriptor (cheaper addressing); otherwise through 64-bit pointers
         const __amdgpu_buffer_rsrc_t rx =
