@@ -893,12 +893,12 @@ int vbcsr_sddmm(const vbcsr_mat *A, const void *dY, int64_t lddy, const void *X,
   if (A->prec == VBCSR_FP64) {
     SddmmParams<double> p{D.rows, D.npanels, D.colx, D.colg, static_cast<const double *>(dY), lddy,
                           static_cast<const double *>(X), ldx, nrhs, static_cast<double *>(dA),
-                          A->N, 0, A->bmax};
+                          A->N, 0, A->nnz};
     err = launch_sddmm_f64(p, s);
   } else {
     SddmmParams<float> p{D.rows, D.npanels, D.colx, D.colg, static_cast<const float *>(dY), lddy,
                          static_cast<const float *>(X), ldx, nrhs, static_cast<float *>(dA),
-                         A->N, 0, A->bmax};
+                         A->N, 0, A->nnz};
     err = launch_sddmm_f32(p, s);
   }
   if (err != hipSuccess) return hip_fail(err, "sddmm kernel launch");
@@ -1013,12 +1013,12 @@ int vbcsr_sddmm_pages(const vbcsr_mat *A, const void *dY, int64_t lddy, const vo
     if (A->prec == VBCSR_FP64) {
       SddmmParams<double> p{D.rows, D.npanels, D.colx, D.colg, static_cast<const double *>(dY),
                             lddy, static_cast<const double *>(X), ldx, nrhs,
-                            static_cast<double *>(dA), A->N, 1, A->bmax};
+                            static_cast<double *>(dA), A->N, 1, A->nnz};
       err = launch_sddmm_f64(p, s);
     } else {
       SddmmParams<float> p{D.rows, D.npanels, D.colx, D.colg, static_cast<const float *>(dY),
                            lddy, static_cast<const float *>(X), ldx, nrhs,
-                           static_cast<float *>(dA), A->N, 1, A->bmax};
+                           static_cast<float *>(dA), A->N, 1, A->nnz};
       err = launch_sddmm_f32(p, s);
     }
     if (err != hipSuccess) return hip_fail(err, "sddmm kernel launch");

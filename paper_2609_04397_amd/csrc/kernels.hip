@@ -1902,23 +1902,31 @@ __global__ void __launch_bounds__(kThreads) k_sddmm_lds(SddmmParams<T> P) {
 // takes 299).  The next step's loads are issued as soon as the fragments are
 // in registers.  Lane (m, kq) holds pieces kq + 4 h of row m for both operands.
 //
-// Stores scattered from the accumulators bound the kernel (20 L2 writes and
-// half the load unit's time per tile), so outputs go through LDS and leave in
-// output order.  PAGE (the forward pages' layout): a tile's outputs are one
-// run, stored 16 bytes a lane.  Graph order: a ring of RS outputs in panel
-// order (block by block, each row-major) with their graph offsets; whole
-// blocks are stored, 64 NS outputs a tile, a block that runs on into the next
-// tile waits for its end.  At most (bj - 1) b wait as a block's first columns
-// and as many for their turn, and a tile spans up to 16 + 2 (bj - 1) columns'
-// outputs: b (3 bmax + 13) <= RS keeps them apart.  NS = 0 stores straight from
-// the accumulators: panels that the ring does not hold (a ring of 1024 leaves
-// two workgroups a compute unit: b = 13, 64 right-hand sides, 77 us against
-// 66).  NS < 0 does so by 64-bit addresses (panels of 1 GiB and more).
+// How the outputs leave, NS > 0 through LDS, NS < 0 straight from the
+// accumulators in -NS stores:
+//   * PAGE (the forward pages' layout), b <= 16: a tile's outputs are one run,
+//     stored 16 bytes a lane.
+//   * PAGE, taller panels, 16 rows at a time: X is the row operand, so that a
+//     lane's column of the tile is a panel row and a store writes 16
+//     consecutive rows of 4 columns (b = 64, 32 right-hand sides, FP32: 281 ->
+//     194 us; b = 33 199 -> 149); the rows left over as in graph order.
+//   * Graph order: 16 columns of 4 rows a store, or through a ring of RS
+//     outputs in panel order (block by block, each row-major) with their graph
+//     offsets; whole blocks are stored, 64 NS outputs a tile, a block that runs
+//     on into the next tile waits for its end.  At most (bj - 1) b wait as a
+//     block's first columns and as many for their turn, and a tile spans up to
+//     16 + 2 (bj - 1) columns' outputs: b (3 bj + 13) < RS keeps them apart and
+//     one entry free, bj the panel's widest block.
+//   * NS = kWide: by 64-bit addresses (panels of 1 GiB and more).
+// The ring's turn through LDS takes as long as a tile's matrix instructions, so
+// it is for outputs that go to memory: see the launcher.
 //
 // b = 1/4/9, K about 150: 32 right-hand sides, FP32, 100 000 panels, graph
 // order 357 -> 299 us, pages 287 -> 238; FP64, 50 000 panels 302 -> 262 and
 // 236 -> 224; 40 right-hand sides FP64 546 -> 394; b = 4/9, 8000 panels, 7
 // right-hand sides, FP64, pages 87 -> 31.
+constexpr int kWide = 0;   // NS of the form with 64-bit addresses
+
 template <typename T, int PR, int NCH, bool PAGE, int RS, int NS>
 __device__ __forceinline__ void sddmm_panel(const SddmmParams<T> &P, const RowDesc &rd, int m0,
                                             uint32_t xbytes, T *xs, T *ring, int32_t *aring) {
@@ -1939,7 +1947,7 @@ __device__ __forceinline__ void sddmm_panel(const SddmmParams<T> &P, const RowDe
   const uint32_t bk = (uint32_t)b * (uint32_t)K;
   const __amdgpu_buffer_rsrc_t ro =
       PAGE ? panel_rsrc(P.dA + rd.vbase, ((bk + 3) & ~3u) * ES)
-           : panel_rsrc(P.dA + (g0 - (int64_t)bk), NS < 0 ? 0 : 2 * bk * ES);
+           : panel_rsrc(P.dA + (g0 - (int64_t)bk), NS == kWide ? 0 : 2 * bk * ES);
   // the 64 / PR lane groups (group = lane / PR) stage rows NIT group + it of a
   // tile with load it; lane i of every four loads the index of row NIT group + i
   const int grp = lane / PR;
@@ -1991,6 +1999,10 @@ __device__ __forceinline__ void sddmm_panel(const SddmmParams<T> &P, const RowDe
       }
   }
   const bool ragged = P.nrhs % EPL != 0;
+  constexpr bool kSwap = PAGE && NS == -4;   // X is the row operand
+  // two chunks a tile: its outputs leave during the next tile's first chunk,
+  // behind that chunk's loads (b = 8, 64 right-hand sides 131 -> 120 us)
+  constexpr bool kLate = PAGE && NS > 0 && NCH == 2;
   const int nt = (K + 15) >> 4;
   int sprev = 0, F = 0;        // first column of the block at a tile's start; outputs flushed
   int32_t uprev = -1;
@@ -2020,7 +2032,7 @@ __device__ __forceinline__ void sddmm_panel(const SddmmParams<T> &P, const RowDe
         if (p < b) ring[m * b + p] = acc[i];
       }
       wave_lds_sync();
-      const uint32_t nst = (uint32_t)(min(K - 16 * j, 16) * b);
+      const uint32_t nst = j < 0 ? 0u : (uint32_t)(min(K - 16 * j, 16) * b);
 #pragma unroll
       for (int i = 0; i < NS; ++i) {
         const uint32_t e = (uint32_t)EPL * (64 * i + lane);
@@ -2042,11 +2054,10 @@ __device__ __forceinline__ void sddmm_panel(const SddmmParams<T> &P, const RowDe
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int p = dst_row<T>(kq, i);
-        if (p < b && k < K) {
-          const int at = (b * sc + p * bj + k - sc) & (RS - 1);
-          ring[at] = acc[i];
-          aring[at] = u + p * bj + (int32_t)bk;
-        }
+        // lanes without an output write to the entry before the oldest one
+        const int at = (p < b && k < K ? b * sc + p * bj + k - sc : F - 1) & (RS - 1);
+        ring[at] = acc[i];
+        aring[at] = u + p * bj + (int32_t)bk;
       }
       wave_lds_sync();
       sprev = __builtin_amdgcn_readlane(sc, 15);
@@ -2057,11 +2068,17 @@ __device__ __forceinline__ void sddmm_panel(const SddmmParams<T> &P, const RowDe
       for (int i = 0; i < NS; ++i) flush(F + 64 * i + lane, E);
       F = min(E, F + 64 * NS);
       wave_lds_sync();
-    } else if constexpr (NS == 0) {
+    } else if constexpr (kSwap) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int c = 16 * j + dst_row<T>(kq, i);
+        put(acc[i], (uint32_t)(c * b + m0 + m), m0 + m < b && c < K);
+      }
+    } else if constexpr (NS < 0) {
       const uint32_t a = PAGE ? (uint32_t)(k * b) : (uint32_t)rel(g) + bk;
       const int bj = PAGE ? 1 : (int)(g.x & 127);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
+      for (int i = 0; i < -NS; ++i) {
         const int p = m0 + dst_row<T>(kq, i);
         put(acc[i], a + (uint32_t)(p * bj), p < b && k < K);
       }
@@ -2094,7 +2111,8 @@ __device__ __forceinline__ void sddmm_panel(const SddmmParams<T> &P, const RowDe
     __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0); vmcnt, expcnt unchanged
   };
   int32_t xn = rows_of(0), xc = xn;
-  v2u32 gc = v2u32{0u, 0u}, gx = gmap_of(0);
+  v2u32 gp{}, gc = v2u32{0u, 0u}, gx = gmap_of(0);
+  V done = V{};   // kLate: sums of the tile before
   int32_t xl = rows_of(1);
   v2u32 gl = gmap_of(1);
   issue(0, 0, xn);
@@ -2104,6 +2122,7 @@ __device__ __forceinline__ void sddmm_panel(const SddmmParams<T> &P, const RowDe
 #pragma unroll
     for (int ch = 0; ch < NCH; ++ch) {
       if (ch == 0) {
+        gp = gc;
         gc = gx;
         gx = gl;
         xc = xn;
@@ -2116,27 +2135,51 @@ __device__ __forceinline__ void sddmm_panel(const SddmmParams<T> &P, const RowDe
         gl = gmap_of(j + 2);
         issue(j + 1, 0, xn);
       }
+      // only arithmetic and LDS accesses may move across: the wait for these
+      // loads counts the stores behind them
+      __builtin_amdgcn_sched_barrier(0x8F);
+      // right-hand sides past nrhs within a piece: what follows in X's row (a
+      // branch: selecting in every step cost 5 % at 64 right-hand sides)
+      if (ragged) {
+#pragma unroll
+        for (int h = 0; h < NIT; ++h) {
+          T *xe = reinterpret_cast<T *>(&bv[h]);
+#pragma unroll
+          for (int e = 0; e < EPL; ++e)
+            xe[e] = EPL * (PR * ch + 4 * h + kq) + e < P.nrhs ? xe[e] : T(0);
+        }
+      }
 #pragma unroll
       for (int h = 0; h < NIT; ++h) {
         const T *xe = reinterpret_cast<const T *>(&bv[h]);
-        const int c = EPL * (PR * ch + 4 * h + kq);
 #pragma unroll
         for (int e = 0; e < EPL; e += 2) {
-          acc0 = mfma(af[ch][h][e], ragged && c + e >= P.nrhs ? T(0) : xe[e], acc0);
-          acc1 = mfma(af[ch][h][e + 1], ragged && c + e + 1 >= P.nrhs ? T(0) : xe[e + 1], acc1);
+          const T a0 = af[ch][h][e], a1 = af[ch][h][e + 1];
+          acc0 = kSwap ? mfma(xe[e], a0, acc0) : mfma(a0, xe[e], acc0);
+          acc1 = kSwap ? mfma(xe[e + 1], a1, acc1) : mfma(a1, xe[e + 1], acc1);
         }
       }
-      if (ch + 1 == NCH) {
+      constexpr auto stores = std::integral_constant<int, (NS < 0 ? -NS : NS)>{};
+      if constexpr (!kLate) {
+        if (ch + 1 < NCH) {
+          fragments(std::integral_constant<int, 0>{});
+          continue;
+        }
 #pragma unroll
         for (int i = 0; i < 4; ++i) acc0[i] += acc1[i];
         out(j, acc0, gc, gx);
-        // NS stores, four without staging, any number by 64-bit addresses
-        fragments(std::integral_constant<int, (NS > 0 ? NS : NS == 0 ? 4 : 0)>{});
+        fragments(stores);
+      } else if (ch == 0) {
+        out(j - 1, done, gp, gc);
+        fragments(stores);
       } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) done[i] = acc0[i] + acc1[i];
         fragments(std::integral_constant<int, 0>{});
       }
     }
   }
+  if constexpr (kLate) out(nt - 1, done, gc, gx);
   if constexpr (!PAGE && NS > 0)
     for (; F < (int)bk; F += 64) flush(F + lane, (int)bk);
 }
@@ -2155,25 +2198,40 @@ k_sddmm(SddmmParams<T> P, uint32_t xbytes) {
   T *xs = xs_all + wave_id() * XE, *ring = ring_all + wave_id() * RS;
   int32_t *ra = aring_all + (PAGE ? 0 : wave_id() * RS);
   const int b = rd.b;
-  const bool big = (int64_t)b * rd.K * (int64_t)sizeof(T) >= (int64_t(1) << 30);
-  if (big) {
+  if ((int64_t)b * rd.K * (int64_t)sizeof(T) >= (int64_t(1) << 30)) {
     for (int m0 = 0; m0 < b; m0 += 16)
+      sddmm_panel<T, PR, NCH, PAGE, RS, kWide>(P, rd, m0, xbytes, xs, ring, ra);
+    return;
+  }
+  if constexpr (PAGE) {
+    if (b <= 16) {
+      if (sizeof(T) == 4 || b <= 8)
+        sddmm_panel<T, PR, NCH, PAGE, RS, 1>(P, rd, 0, xbytes, xs, ring, ra);
+      else
+        sddmm_panel<T, PR, NCH, PAGE, RS, 2>(P, rd, 0, xbytes, xs, ring, ra);
+      return;
+    }
+  } else if constexpr (RS > 1) {
+    // the panel's columns are in ascending order of their blocks' widths
+    const int bj = (int)(P.colg[rd.cbase + rd.K - 1] & 127);
+    if (b <= 12 && b * (3 * bj + 13) < RS) {
+      if (b <= 4)
+        sddmm_panel<T, PR, NCH, PAGE, RS, 1>(P, rd, 0, xbytes, xs, ring, ra);
+      else
+        sddmm_panel<T, PR, NCH, PAGE, RS, 3>(P, rd, 0, xbytes, xs, ring, ra);
+      return;
+    }
+  }
+  // straight from the accumulators: element i of a lane holds row kq + 4 i in
+  // FP64 and 4 kq + i in FP32
+  for (int m0 = 0; m0 < b; m0 += 16) {
+    const int n = sizeof(T) == 8 ? (b - m0 + 3) / 4 : b - m0;
+    if (n == 1)
       sddmm_panel<T, PR, NCH, PAGE, RS, -1>(P, rd, m0, xbytes, xs, ring, ra);
-  } else if (PAGE ? b > 16 : b > 16 || b * (3 * P.bmax + 13) > RS) {
-    for (int m0 = 0; m0 < b; m0 += 16)
-      sddmm_panel<T, PR, NCH, PAGE, RS, 0>(P, rd, m0, xbytes, xs, ring, ra);
-  } else if constexpr (PAGE) {
-    if (sizeof(T) == 4 || b <= 8)
-      sddmm_panel<T, PR, NCH, PAGE, RS, 1>(P, rd, 0, xbytes, xs, ring, ra);
+    else if (n == 2)
+      sddmm_panel<T, PR, NCH, PAGE, RS, -2>(P, rd, m0, xbytes, xs, ring, ra);
     else
-      sddmm_panel<T, PR, NCH, PAGE, RS, 2>(P, rd, 0, xbytes, xs, ring, ra);
-  } else {
-    if (b <= 4)
-      sddmm_panel<T, PR, NCH, PAGE, RS, 1>(P, rd, 0, xbytes, xs, ring, ra);
-    else if (b <= 12)
-      sddmm_panel<T, PR, NCH, PAGE, RS, 3>(P, rd, 0, xbytes, xs, ring, ra);
-    else
-      sddmm_panel<T, PR, NCH, PAGE, RS, 4>(P, rd, 0, xbytes, xs, ring, ra);
+      sddmm_panel<T, PR, NCH, PAGE, RS, -4>(P, rd, m0, xbytes, xs, ring, ra);
   }
 }
 
@@ -2716,12 +2774,22 @@ hipError_t launch_pack(const PackParams &p, const void *src, int src_dtype, hipS
   return hipGetLastError();
 }
 
+// Outputs in graph order take the ring where they are too large for the 256 MB
+// Infinity Cache; us straight from the accumulators and through the ring: FP32,
+// 32 right-hand sides, b = 8 (250 MB) 196/174, b = 4/9 (205 MB) 217/188, b =
+// 1/4/9 (142 MB) 114/133, b = 5 (122 MB) 99/124; FP64, 16, b = 4/9 (410 MB)
+// 268/256, b = 1/4/9 (283 MB) 201/194, b = 8 (150 MB) 49/70, 1,000 rows of b =
+// 5 12/19.  FP64 beyond 32 right-hand sides never: b = 8, 48, 500 MB 367/403.
+constexpr int64_t kRingBytes = 192 << 20;
+
 template <typename T, int PR, int NCH>
 void launch_sddmm_tiles(const SddmmParams<T> &p, dim3 grid, uint32_t xbytes, hipStream_t s) {
   if (p.page_out)
     hipLaunchKernelGGL((k_sddmm<T, PR, NCH, true, 256>), grid, dim3(kThreads), 0, s, p, xbytes);
+  else if (NCH == 1 && p.nnz * (int64_t)sizeof(T) >= kRingBytes)
+    hipLaunchKernelGGL((k_sddmm<T, PR, NCH, false, NCH == 1 ? 512 : 1>), grid, dim3(kThreads), 0, s, p, xbytes);
   else
-    hipLaunchKernelGGL((k_sddmm<T, PR, NCH, false, 512>), grid, dim3(kThreads), 0, s, p, xbytes);
+    hipLaunchKernelGGL((k_sddmm<T, PR, NCH, false, 1>), grid, dim3(kThreads), 0, s, p, xbytes);
 }
 
 template <typename T>

@@ -109,7 +109,7 @@ struct SddmmParams {
   T *dA;
   int64_t xrows;         // rows of X (columns of the operator)
   int32_t page_out;      // 1: dA in the forward pages' layout (colg unused)
-  int32_t bmax;          // largest block size of the operator
+  int64_t nnz;           // values of dA
 };
 hipError_t launch_sddmm_f64(const SddmmParams<double> &p, hipStream_t s);
 hipError_t launch_sddmm_f32(const SddmmParams<float> &p, hipStream_t s);
