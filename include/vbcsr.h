@@ -33,7 +33,7 @@
  * products on different streams may run concurrently on one handle, but
  * must not overlap a vbcsr_set_values on it.
  *
- * Device memory: blocks of destroyed vbcsr_mat handles and of calls'
+ * Device memory: blocks of destroyed handles (vbcsr_mat and vbcsr_zmat) and of calls'
  * temporaries are kept for later calls, at most 1/64 of the device's memory,
  * while the library holds other memory on the device; they are returned when
  * an allocation fails and with the last handle.

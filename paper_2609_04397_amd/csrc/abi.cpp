@@ -126,7 +126,9 @@ DevCache &dev_cache() {
   return *c;
 }
 
-int dev_alloc(void **p, size_t bytes) {
+}  // namespace
+
+int vbcsr::dev_alloc(void **p, size_t bytes) {
   *p = nullptr;
   const char *lim = std::getenv("VBCSR_FAIL_ALLOC_AFTER");
   const long n = g_alloc_count.fetch_add(1);
@@ -178,10 +180,7 @@ int dev_alloc(void **p, size_t bytes) {
   return VBCSR_OK;
 }
 
-// Give back a block of dev_alloc.  `idle`: the caller has synchronised the
-// current device since the block's last use; otherwise (and for a block of
-// another device) it is freed, which waits by itself.
-void dev_free(void *p, bool idle) noexcept {
+void vbcsr::dev_free(void *p, bool idle) noexcept {
   if (!p) return;
   int cur = -1;
   (void)hipGetDevice(&cur);
@@ -216,6 +215,8 @@ void dev_free(void *p, bool idle) noexcept {
   if (!keep) (void)hipFree(blk.p);
   if (left == 0) c.release(blk.dev, 0);
 }
+
+namespace {
 
 template <typename T>
 int upload(T **dst, const T *src, size_t count, hipStream_t s) {

@@ -6,6 +6,7 @@
 #include <array>
 #include <atomic>
 #include <exception>
+#include <cstddef>
 #include <cstdint>
 #include <memory>
 #include <mutex>
@@ -153,6 +154,15 @@ int set_error(int code, const std::string &msg);
 // flight (ENOMEM for host allocation and thread-resource failures, EINVAL
 // otherwise), with `where` and its message recorded as the last error.
 int api_exception(const char *where);
+
+// Device memory of every handle and of calls' temporaries: a status (with the
+// last error recorded) and the block, or a null pointer for 0 bytes.  Blocks
+// that are given back may be kept for later calls; contents are undefined.
+int dev_alloc(void **p, size_t bytes);
+// Give back a block of dev_alloc.  `idle`: the caller has synchronised the
+// current device since the block's last use; otherwise (and for a block of
+// another device) it is freed, which waits by itself.
+void dev_free(void *p, bool idle) noexcept;
 
 // Rows that 16-row tiles take for panels of these heights over those that
 // 4-row tiles take (1 to 4): what the small tiles save.

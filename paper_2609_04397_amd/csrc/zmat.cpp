@@ -46,16 +46,9 @@ int zhip(hipError_t e, const char *where) {
 
 template <typename T>
 int zalloc(vbcsr_zmat *Z, T **p, size_t count) {
-  *p = nullptr;
-  if (count == 0) return VBCSR_OK;
-  hipError_t e = hipMalloc(reinterpret_cast<void **>(p), sizeof(T) * count);
-  if (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation) {
-    (void)hipGetLastError();
-    return zfail(VBCSR_ENOMEM, "hipMalloc of " + std::to_string(sizeof(T) * count) + " bytes failed");
-  }
-  if (e != hipSuccess) return zhip(e, "hipMalloc");
-  Z->owned.push_back(*p);
-  return VBCSR_OK;
+  int rc = dev_alloc(reinterpret_cast<void **>(p), sizeof(T) * count);
+  if (rc == VBCSR_OK && *p) Z->owned.push_back(*p);
+  return rc;
 }
 
 template <typename T>
@@ -67,8 +60,8 @@ int zup(vbcsr_zmat *Z, T **p, const T *src, size_t count, hipStream_t s) {
 }
 
 void zfree(vbcsr_zmat *Z) {
-  if (!Z->owned.empty()) (void)hipDeviceSynchronize();
-  for (void *p : Z->owned) (void)hipFree(p);
+  const bool idle = Z->owned.empty() || hipDeviceSynchronize() == hipSuccess;
+  for (void *p : Z->owned) dev_free(p, idle);
   Z->owned.clear();
 }
 

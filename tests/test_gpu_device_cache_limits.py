@@ -1,0 +1,66 @@
+"""Limits of the device memory kept between calls, over both kinds of handle."""
+import gc
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2609_04397_amd.kspace import KMatrix
+from paper_2609_04397_amd.matrix import Matrix
+
+pytestmark = pytest.mark.gpu
+
+
+def ring_graph(n, per_row, b):
+    """n atoms of b with blocks at i, i + 1, ... i + per_row - 1 (modulo n)."""
+    rp = np.arange(0, per_row * n + 1, per_row, dtype=np.int64)
+    ci = np.sort((np.arange(n)[:, None] + np.arange(per_row)[None, :]) % n, axis=1)
+    return np.full(n, b, np.int32), rp, ci.astype(np.int32).ravel()
+
+
+def free_bytes():
+    gc.collect()
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    return torch.cuda.mem_get_info()
+
+
+def complex_handle(n, per_row, b):
+    g = ring_graph(n, per_row, b)
+    return KMatrix(*g, np.zeros(g[2].size, np.int32), np.zeros((1, 3), np.int32))
+
+
+def test_complex_handles_take_and_leave_kept_blocks():
+    """16 bytes a value and direction and 8 for the real ones: 1.28 GB."""
+    anchor = Matrix(*ring_graph(4, 2, 3))
+    start = free_bytes()[0]
+    K = complex_handle(4000, 20, 20)
+    used = start - free_bytes()[0]
+    assert used > 1 << 30
+    K.close()
+    kept = start - free_bytes()[0]
+    assert kept > 1 << 30                         # its blocks stay
+    K = complex_handle(4000, 20, 20)
+    assert start - free_bytes()[0] <= used + (64 << 20)   # and serve the next one
+    K.close()
+    anchor.close()
+    assert start - free_bytes()[0] <= 64 << 20
+
+
+def test_complex_handle_gets_memory_that_is_kept():
+    """With less free than a complex handle takes, the kept blocks of a real
+    one (none of a size that could be reused) make room for it."""
+    anchor = Matrix(*ring_graph(4, 2, 3))
+    M = Matrix(*ring_graph(8000, 50, 20))         # two sets of pages of 1.28 GB
+    M.close()
+    filler = []
+    try:
+        leave = 1 << 30
+        filler.append(torch.empty(free_bytes()[0] - leave, dtype=torch.uint8, device="cuda"))
+        # pages of 0.97 GB in each direction and values of 0.49
+        K = complex_handle(4000, 38, 20)
+        K.close()
+    finally:
+        filler.clear()
+        free_bytes()
+        anchor.close()
