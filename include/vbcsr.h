@@ -33,10 +33,12 @@
  * products on different streams may run concurrently on one handle, but
  * must not overlap a vbcsr_set_values on it.
  *
- * Device memory: blocks of destroyed handles (vbcsr_mat and vbcsr_zmat) and of calls'
- * temporaries are kept for later calls, at most 1/64 of the device's memory,
- * while the library holds other memory on the device; they are returned when
- * an allocation fails and with the last handle.
+ * Device memory: blocks of destroyed handles (vbcsr_mat and vbcsr_zmat) and
+ * of calls' temporaries are kept for later calls while the library holds
+ * other memory on the device.  A block may serve a request that is up to a
+ * quarter (or 1 MiB) smaller; that surplus and the blocks kept are together
+ * at most 1/64 of the device's memory.  Kept blocks are returned when an
+ * allocation of the library fails and with the last handle.
  */
 #ifndef VBCSR_H
 #define VBCSR_H

@@ -93,31 +93,47 @@ std::atomic<long> g_alloc_count{0};
 //   * A block is kept only once nothing on its device can still use it (the
 //     callers of dev_free have synchronised the device), so it may go to any
 //     stream and thread.  Contents are never relied on.
-//   * At most 1/64 of the device's memory (4.5 GB here) is kept, the oldest
-//     blocks going first; all of it is returned when an allocation fails and
-//     when the library holds no other block on the device.
+//   * What is kept and what blocks handed out again have beyond their requests
+//     is together at most 1/64 of the device's memory (4.5 GiB here), each kept
+//     block counted in whole pages, and at most kMaxKept blocks are kept, so
+//     that the search below stays short; the oldest go first.  All of it is
+//     returned when an allocation fails and when the library holds no other
+//     block on the device.
 //   * A request takes the smallest kept block that is at most a quarter (or
 //     1 MiB) larger than it.
 struct DevCache {
   struct Block {
     void *p;
-    size_t bytes;
+    size_t bytes, asked;   // size, and what its present user asked for
     int dev;
   };
+  struct Device {
+    size_t limit = 0, held = 0, surplus = 0, n_out = 0, n_kept = 0;
+  };
+  static constexpr size_t kMaxKept = 1024, kPage = 4096;
   std::mutex mu;
-  std::vector<Block> kept;                              // oldest first
-  std::unordered_map<void *, Block> out;                // handed out
-  std::unordered_map<int, size_t> limit, held, n_out;   // per device
+  std::vector<Block> kept;                 // oldest first
+  std::unordered_map<void *, Block> out;   // handed out
+  std::unordered_map<int, Device> on;
 
-  void release(int dev, size_t over) {   // free kept blocks of dev until held <= over
-    for (size_t i = 0; i < kept.size() && held[dev] > over;) {
-      if (kept[i].dev != dev) {
+  static size_t charge(const Block &b) { return (b.bytes + kPage - 1) / kPage * kPage; }
+
+  Block take(size_t i) {
+    const Block b = kept[i];
+    Device &d = on[b.dev];
+    d.held -= charge(b);
+    --d.n_kept;
+    kept.erase(kept.begin() + (std::ptrdiff_t)i);
+    return b;
+  }
+  // free kept blocks of dev until at most `bytes` and `count` are left
+  void release(int dev, size_t bytes, size_t count) {
+    const Device &d = on[dev];
+    for (size_t i = 0; i < kept.size() && (d.held > bytes || d.n_kept > count);) {
+      if (kept[i].dev == dev)
+        (void)hipFree(take(i).p);
+      else
         ++i;
-        continue;
-      }
-      held[dev] -= kept[i].bytes;
-      (void)hipFree(kept[i].p);
-      kept.erase(kept.begin() + (std::ptrdiff_t)i);
     }
   }
 };
@@ -145,16 +161,17 @@ int vbcsr::dev_alloc(void **p, size_t bytes) {
         (best == c.kept.size() || k.bytes < c.kept[best].bytes))
       best = i;
   }
-  DevCache::Block blk{nullptr, bytes, dev};
+  DevCache::Block blk{nullptr, bytes, bytes, dev};
   const bool reuse = best < c.kept.size();
-  if (reuse) blk = c.kept[best];
   // room for the bookkeeping first: nothing below it can throw
-  auto slot = c.out.end();
-  if (!reuse) {
+  DevCache::Device &d = c.on[dev];
+  if (reuse) {
+    blk = c.kept[best];
+  } else {
     hipError_t e = hipMalloc(&blk.p, bytes);
     if (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation) {
       (void)hipGetLastError();
-      c.release(dev, 0);
+      c.release(dev, 0, 0);
       e = hipMalloc(&blk.p, bytes);
     }
     if (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation) {
@@ -163,20 +180,17 @@ int vbcsr::dev_alloc(void **p, size_t bytes) {
     }
     if (e != hipSuccess) return hip_fail(e, "hipMalloc");
   }
+  blk.asked = bytes;
   try {
-    c.held[dev];
-    c.n_out[dev];
-    slot = c.out.emplace(blk.p, blk).first;
+    c.out.emplace(blk.p, blk);
   } catch (...) {
     if (!reuse) (void)hipFree(blk.p);
     throw;
   }
-  if (reuse) {
-    c.held[dev] -= blk.bytes;
-    c.kept.erase(c.kept.begin() + (std::ptrdiff_t)best);
-  }
-  ++c.n_out[dev];
-  *p = slot->first;
+  if (reuse) (void)c.take(best);
+  d.surplus += blk.bytes - bytes;
+  ++d.n_out;
+  *p = blk.p;
   return VBCSR_OK;
 }
 
@@ -193,27 +207,30 @@ void vbcsr::dev_free(void *p, bool idle) noexcept {
   }
   const DevCache::Block blk = it->second;
   c.out.erase(it);
-  const size_t left = --c.n_out[blk.dev];
-  bool keep = idle && blk.dev == cur && left > 0;
+  DevCache::Device &d = c.on[blk.dev];   // made by dev_alloc
+  d.surplus -= blk.bytes - blk.asked;
+  --d.n_out;
+  bool keep = idle && blk.dev == cur && d.n_out > 0;
   if (keep) {
-    try {
-      size_t &lim = c.limit[blk.dev];
-      if (lim == 0) {
-        size_t avail = 0, total = 0;
-        lim = hipMemGetInfo(&avail, &total) == hipSuccess ? std::max<size_t>(total / 64, 1) : 1;
-      }
-      keep = blk.bytes <= lim;
-      if (keep) {
-        c.release(blk.dev, lim - blk.bytes);
+    if (d.limit == 0) {
+      size_t avail = 0, total = 0;
+      d.limit = hipMemGetInfo(&avail, &total) == hipSuccess ? std::max<size_t>(total / 64, 1) : 1;
+    }
+    const size_t need = DevCache::charge(blk) + d.surplus;
+    keep = need <= d.limit;
+    if (keep) {
+      c.release(blk.dev, d.limit - need, DevCache::kMaxKept - 1);
+      try {
         c.kept.push_back(blk);
-        c.held[blk.dev] += blk.bytes;
+        d.held += DevCache::charge(blk);
+        ++d.n_kept;
+      } catch (...) {
+        keep = false;
       }
-    } catch (...) {
-      keep = false;
     }
   }
   if (!keep) (void)hipFree(blk.p);
-  if (left == 0) c.release(blk.dev, 0);
+  if (d.n_out == 0) c.release(blk.dev, 0, 0);
 }
 
 namespace {

@@ -64,3 +64,42 @@ def test_complex_handle_gets_memory_that_is_kept():
         filler.clear()
         free_bytes()
         anchor.close()
+
+
+def test_larger_blocks_in_use_count_towards_the_bound():
+    """Handles that take blocks a fifth larger than their own, generation
+    after generation: what is withheld in all stays below 1/64 of the device."""
+    big, small = ring_graph(5400, 50, 20), ring_graph(5400, 41, 20)   # 0.86 and 0.71 GB of pages, twice
+
+    def handles(g, n):
+        return [Matrix(*g) for _ in range(n)]
+
+    anchor = Matrix(*ring_graph(4, 2, 3))
+    free_bytes()
+    start, total = free_bytes()
+    mine = []
+    for _ in range(8):
+        for h in handles(big, 3):
+            h.close()
+        mine += handles(small, 3)
+    withheld = start - free_bytes()[0] - len(mine) * (2 * small[2].size * 400 * 8)
+    # and tables of less than 64 MiB a handle
+    assert withheld <= total // 64 + (len(mine) * (64 << 20))
+    for h in mine:
+        h.close()
+    anchor.close()
+    assert start - free_bytes()[0] <= 64 << 20
+
+
+def test_small_blocks_kept_are_bounded_in_number():
+    """1,500 closed handles of about 20 blocks: at most 1,024 stay."""
+    anchor = Matrix(*ring_graph(4, 2, 3))
+    start = free_bytes()[0]
+    hs = [Matrix(*ring_graph(4, 2, 3)) for _ in range(1500)]
+    used = start - free_bytes()[0]
+    for h in hs:
+        h.close()
+    kept = start - free_bytes()[0]
+    anchor.close()
+    assert used > 64 << 20
+    assert kept <= 16 << 20                       # pages of 4 KiB
