@@ -38,7 +38,9 @@
  * other memory on the device.  A block may serve a request that is up to a
  * quarter (or 1 MiB) smaller; that surplus and the blocks kept are together
  * at most 1/64 of the device's memory.  Kept blocks are returned when an
- * allocation of the library fails and with the last handle.
+ * allocation of the library fails, with the last handle, and by
+ * vbcsr_release_memory, which a caller uses before it allocates nearly all of
+ * the device itself.
  */
 #ifndef VBCSR_H
 #define VBCSR_H
@@ -671,6 +673,11 @@ void vbcsr_zmat_destroy(vbcsr_zmat *Z);
 /* vbcsr_destroy -- free a handle (NULL is ignored); synchronises the device.
  * Library utility: no passage of the paper defines it. */
 void vbcsr_destroy(vbcsr_mat *A);
+
+/* vbcsr_release_memory -- (library utility; no passage of the paper defines
+ * it) return the device memory kept between calls on the current device;
+ * `bytes` (may be NULL) receives how much it was. */
+int vbcsr_release_memory(int64_t *bytes);
 
 /* vbcsr_last_error -- (library utility; no passage of the paper defines it)
  * message of the last non-OK status on this thread

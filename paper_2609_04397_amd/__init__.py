@@ -4,11 +4,11 @@
 the package itself touches neither.
 """
 
-__all__ = ["Matrix", "spmm", "spmm_pages", "Halo", "VbcsrError"]
+__all__ = ["Matrix", "spmm", "spmm_pages", "Halo", "VbcsrError", "release_memory"]
 
 
 def __getattr__(name):
-    if name in ("Matrix", "spmm", "spmm_pages"):
+    if name in ("Matrix", "spmm", "spmm_pages", "release_memory"):
         from . import matrix
         return getattr(matrix, name)
     if name == "Halo":

@@ -100,6 +100,7 @@ SIGNATURES = {
     "vbcsr_zmat_get_values": (_int, [_p, _p, _p]),
     "vbcsr_zmat_destroy": (None, [_p]),
     "vbcsr_destroy": (None, [_p]),
+    "vbcsr_release_memory": (_int, [ctypes.POINTER(_i64)]),
     "vbcsr_last_error": (ctypes.c_char_p, []),
 }
 

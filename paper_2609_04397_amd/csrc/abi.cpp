@@ -1328,6 +1328,20 @@ int vbcsr_info(const vbcsr_mat *A, int64_t *n_rows, int64_t *nnzb, int64_t *n_va
   return api_exception("vbcsr_info");
 }
 
+int vbcsr_release_memory(int64_t *bytes) try {
+  int dev = 0;
+  HIP_TRY(hipGetDevice(&dev), "hipGetDevice");
+  DevCache &c = dev_cache();
+  std::lock_guard<std::mutex> lock(c.mu);
+  const auto d = c.on.find(dev);
+  const size_t held = d == c.on.end() ? 0 : d->second.held;
+  if (held) c.release(dev, 0, 0);
+  if (bytes) *bytes = (int64_t)held;
+  return VBCSR_OK;
+} catch (...) {
+  return api_exception("vbcsr_release_memory");
+}
+
 void vbcsr_destroy(vbcsr_mat *A) {
   if (!A) return;
   free_all(A);

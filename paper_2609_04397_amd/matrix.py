@@ -406,3 +406,11 @@ def spmm_pages(pages, X, A: Matrix):
     """Differentiable ``A(pages) @ X`` with the values held in the operator's
     forward-page layout (``A.page_size`` entries, zero gaps)."""
     return _SpmmPagesFunction.apply(pages, X, A)
+
+
+def release_memory() -> int:
+    """Return the device memory that the library keeps between calls on the
+    current device; the bytes that it was."""
+    n = ctypes.c_int64()
+    check(_lib.load().vbcsr_release_memory(ctypes.byref(n)))
+    return n.value

@@ -103,3 +103,20 @@ def test_small_blocks_kept_are_bounded_in_number():
     anchor.close()
     assert used > 64 << 20
     assert kept <= 16 << 20                       # pages of 4 KiB
+
+
+def test_kept_memory_is_released_on_demand():
+    """An allocation of a caller's own that fits only beside an empty set."""
+    from paper_2609_04397_amd import release_memory
+    anchor = Matrix(*ring_graph(4, 2, 3))
+    release_memory()
+    free = free_bytes()[0]
+    Matrix(*ring_graph(8000, 25, 20)).close()     # two sets of pages of 0.64 GB
+    kept = free - free_bytes()[0]
+    assert kept > 1 << 30
+    got = release_memory()
+    assert abs(got - kept) <= 64 << 20
+    assert free - free_bytes()[0] <= 64 << 20
+    assert release_memory() == 0
+    assert anchor.spmm(torch.ones((12, 1), dtype=torch.float64, device="cuda")).shape == (12, 1)
+    anchor.close()
