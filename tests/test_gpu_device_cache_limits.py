@@ -120,3 +120,24 @@ def test_kept_memory_is_released_on_demand():
     assert release_memory() == 0
     assert anchor.spmm(torch.ones((12, 1), dtype=torch.float64, device="cuda")).shape == (12, 1)
     anchor.close()
+
+
+@pytest.mark.parametrize("per_row,reused", [(25, True), (21, True), (19, False)])
+def test_kept_blocks_serve_requests_up_to_a_quarter_smaller(per_row, reused):
+    """Pages of 0.64 GB kept; 0.64, 0.54 (1.19 times smaller) and 0.49 (1.32)
+    asked for: growth of nothing, nothing, and two sets of pages."""
+    from paper_2609_04397_amd import release_memory
+    anchor = Matrix(*ring_graph(4, 2, 3))
+    release_memory()
+    start = free_bytes()[0]
+    Matrix(*ring_graph(4000, 50, 20)).close()
+    kept = start - free_bytes()[0]
+    assert kept >= 2 * 640_000_000
+    h = Matrix(*ring_graph(4000, 2 * per_row, 20))
+    growth = start - free_bytes()[0] - kept
+    if reused:
+        assert growth <= 64 << 20
+    else:
+        assert growth >= 900_000_000
+    h.close()
+    anchor.close()

@@ -70,3 +70,24 @@ def test_ring_with_narrow_panels_beside_wide_ones():
 def test_tall_panels_in_both_layouts(prec):
     b, rp, ci = graph(60, 12, (1, 15, 16, 17, 20, 31, 32, 33, 47, 63, 64), 5)
     check(b, rp, ci, prec, (1, 3, 8, 31, 32, 33, 63, 64), 0)
+
+
+@pytest.mark.parametrize("prec,full,part", [("fp64", 16, 10), ("fp64", 64, 34), ("fp32", 32, 20),
+                                            ("fp32", 64, 40)])
+def test_staged_pieces_past_the_right_hand_sides_read_zero(prec, full, part):
+    """LDS holds NaN from a call that used all pieces of a row; one that uses
+    fewer of them, whole, gives the sums of its own."""
+    b, rp, ci = graph(3000, 12, (4, 9, 13), 6)
+    A = Matrix(b, rp, ci, prec=prec)
+    dt = torch.float64 if prec == "fp64" else torch.float32
+    rng = np.random.default_rng(2)
+    X = torch.from_numpy(rng.standard_normal((A.N, part))).to("cuda", dt)
+    G = torch.from_numpy(rng.standard_normal((A.N, part))).to("cuda", dt)
+    bad = torch.full((A.N, full), float("nan"), dtype=dt, device="cuda")
+    first = A.sddmm(G, X), A.sddmm_pages(G, X)
+    assert bool(torch.isnan(A.sddmm(bad, bad)).all())
+    again = A.sddmm(G, X)
+    A.sddmm_pages(bad, bad)
+    pages = A.sddmm_pages(G, X)
+    assert bool(torch.isfinite(again).all()) and torch.equal(again, first[0])
+    assert bool(torch.isfinite(pages[:-2]).all()) and torch.equal(pages[:-2], first[1][:-2])
