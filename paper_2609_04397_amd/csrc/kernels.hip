@@ -1806,7 +1806,7 @@ __global__ void __launch_bounds__(kThreads) k_sddmm_lds(SddmmParams<T> P) {
   const int32_t *__restrict__ cx = P.colx + rd.cbase;
   const int64_t *__restrict__ cg = P.colg + rd.cbase;
   const __amdgpu_buffer_rsrc_t rx =
-      panel_rsrc(P.X, (uint32_t)(P.xrows * P.ldx * (int64_t)sizeof(T)));
+      panel_rsrc(P.X, (uint32_t)(((P.xrows - 1) * P.ldx + P.nrhs) * (int64_t)sizeof(T)));
   // contraction order inside a 32-wide chunk (the same for both operands):
   // FP64 c = 8 l + 2 kq + e (l < 4, e < 2), FP32 c = 8 kq + s
   constexpr bool PAIR = sizeof(T) == 8;
