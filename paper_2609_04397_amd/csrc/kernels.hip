@@ -1780,17 +1780,19 @@ __global__ void __launch_bounds__(kThreads) k_sddmm_mfma(SddmmParams<T> P) {
 // per instruction, written to a wave-private LDS tile (rows padded by EPL
 // elements, so the fragment reads of the 16 rows hit distinct banks) and read
 // back in the MFMA fragment order.  For more than 64 right-hand sides, in
-// passes.  X is addressed through one buffer
-// descriptor (all of X within 2^31 bytes): reads past its end return zero.
-template <typename T, int CW>
+// passes of CW (and for 33 to 64 with a leading dimension of dY of 2^22 or
+// more, which the kernel below does not address).  X is addressed through one
+// buffer descriptor (all of X within 2^31 bytes): reads past its end return
+// zero.
+template <typename T>
 __global__ void __launch_bounds__(kThreads) k_sddmm_lds(SddmmParams<T> P) {
   using V = typename Frag<T>::type;
+  constexpr int CW = 64;                       // right-hand sides per pass
   constexpr int NCH = CW / 32;                 // 32-wide chunks per pass
   constexpr int EPL = 16 / (int)sizeof(T);     // elements per 16-byte piece
   constexpr int LPR = CW / EPL;                // lanes per staged row
   constexpr int RPI = 64 / LPR;                // rows per staging load
   constexpr int RS = CW + EPL;                 // LDS row stride (elements)
-  static_assert(CW == 32 || CW == 64, "pass width");
   __shared__ __align__(16) T xs_all[kWaves * 16 * RS];
   const int row = xcd_remap(blockIdx.x, gridDim.x) * kWaves + wave_id();
   if (row >= P.nrows) return;
@@ -2812,7 +2814,7 @@ hipError_t launch_sddmm_t(const SddmmParams<T> &p, hipStream_t s) {
     return hipGetLastError();
   }
   if (p.nrhs > 32 && p.xrows * p.ldx * (int64_t)sizeof(T) < (int64_t(1) << 31)) {
-    hipLaunchKernelGGL((k_sddmm_lds<T, 64>), grid, dim3(kThreads), 0, s, p);
+    hipLaunchKernelGGL((k_sddmm_lds<T>), grid, dim3(kThreads), 0, s, p);
     return hipGetLastError();
   }
   // right-hand sides beyond the register-resident chunks are loaded per tile
