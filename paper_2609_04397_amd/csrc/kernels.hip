@@ -1919,6 +1919,10 @@ __global__ void __launch_bounds__(kThreads) k_sddmm_lds(SddmmParams<T> P) {
 //     block's first columns and as many for their turn, and a tile spans up to
 //     16 + 2 (bj - 1) columns' outputs: b (3 bj + 13) < RS keeps them apart and
 //     one entry free, bj the panel's widest block.
+//   * NS = kHold (FP64, graph order, b = 11 to 47, outputs that go to
+//     memory): the columns of a block that runs on into the next tile wait for
+//     it in registers, so that a block's lines are written at once (b = 13, 64
+//     right-hand sides, 32,768 rows: 638 -> 603 us; 13,824 rows 273 -> 258).
 //   * NS = kWide: by 64-bit addresses (panels of 1 GiB and more).
 // The ring's turn through LDS takes as long as a tile's matrix instructions, so
 // it is for outputs that go to memory: see the launcher.
@@ -1927,7 +1931,10 @@ __global__ void __launch_bounds__(kThreads) k_sddmm_lds(SddmmParams<T> P) {
 // order 357 -> 299 us, pages 287 -> 238; FP64, 50 000 panels 302 -> 262 and
 // 236 -> 224; 40 right-hand sides FP64 546 -> 394; b = 4/9, 8000 panels, 7
 // right-hand sides, FP64, pages 87 -> 31.
-constexpr int kWide = 0;   // NS of the form with 64-bit addresses
+// Values of NS: the form that holds outputs back, and that with 64-bit addresses.
+constexpr int kHold = -8, kWide = 0;
+// Outputs of this size and more go to memory, not to the 256 MB Infinity Cache.
+constexpr int64_t kMemoryBytes = 192 << 20;
 
 template <typename T, int PR, int NCH, bool PAGE, int RS, int NS>
 __device__ __forceinline__ void sddmm_panel(const SddmmParams<T> &P, const RowDesc &rd, int m0,
@@ -2021,6 +2028,11 @@ __device__ __forceinline__ void sddmm_panel(const SddmmParams<T> &P, const RowDe
     else
       __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), ro, off, 0, 0);
   };
+  // kHold: sums of the tile before whose block runs on, in lanes m >= csplit
+  V carry = V{};
+  bool held = false;
+  uint32_t ca = 0;
+  int cbj = 0, csplit = 16;
   auto flush = [&](int e, int E) {
     const T v = ring[e & (RS - 1)];
     put(v, (uint32_t)aring[e & (RS - 1)], e < E);
@@ -2076,6 +2088,32 @@ __device__ __forceinline__ void sddmm_panel(const SddmmParams<T> &P, const RowDe
         const int c = 16 * j + dst_row<T>(kq, i);
         put(acc[i], (uint32_t)(c * b + m0 + m), m0 + m < b && c < K);
       }
+    } else if constexpr (NS == kHold) {
+      const int32_t u = rel(g);
+      const int bj = (int)(g.x & 127);
+      const uint32_t a = (uint32_t)u + bk;
+      const int32_t up = __builtin_amdgcn_update_dpp(u, u, 0x111, 0xF, 0xF, false);  // row_shr:1
+      const uint32_t brk = ((uint32_t)__ballot(u != up + 1) & 0xFFFFu) | 1u;
+      const bool cont = j + 1 < nt && __builtin_amdgcn_readlane(rel(gn), 0) ==
+                                          __builtin_amdgcn_readlane(u, 15) + 1;
+      const int split = cont ? 31 - __builtin_clz(brk) : 16;
+      if (csplit < 16) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int p = m0 + dst_row<T>(kq, i);
+          put(carry[i], ca + (uint32_t)(p * cbj), p < b && m >= csplit);
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int p = m0 + dst_row<T>(kq, i);
+        put(acc[i], a + (uint32_t)(p * bj), p < b && k < K && m < split);
+      }
+      held = csplit < 16;
+      carry = acc;
+      ca = a;
+      cbj = bj;
+      csplit = split;
     } else if constexpr (NS < 0) {
       const uint32_t a = PAGE ? (uint32_t)(k * b) : (uint32_t)rel(g) + bk;
       const int bj = PAGE ? 1 : (int)(g.x & 127);
@@ -2105,7 +2143,14 @@ __device__ __forceinline__ void sddmm_panel(const SddmmParams<T> &P, const RowDe
   L16 bv[NIT];
   auto fragments = [&](auto behind) {   // stores issued since the rows' loads
     // vmcnt(behind): the rows are in LDS; expcnt, lgkmcnt unchanged
-    __builtin_amdgcn_s_waitcnt(0x0F70 | decltype(behind)::value);
+    if constexpr (NS == kHold && decltype(behind)::value != 0) {
+      if (held)
+        __builtin_amdgcn_s_waitcnt(0x0F78);
+      else
+        __builtin_amdgcn_s_waitcnt(0x0F74);
+    } else {
+      __builtin_amdgcn_s_waitcnt(0x0F70 | decltype(behind)::value);
+    }
 #pragma unroll
     for (int h = 0; h < NIT; ++h)
       bv[h] = *reinterpret_cast<const L16 *>(xm + EPL * ((kq + 4 * h) ^ perm(m)));
@@ -2226,7 +2271,13 @@ k_sddmm(SddmmParams<T> P, uint32_t xbytes) {
   }
   // straight from the accumulators: element i of a lane holds row kq + 4 i in
   // FP64 and 4 kq + i in FP32
-  for (int m0 = 0; m0 < b; m0 += 16) {
+  int m0 = 0;
+  if constexpr (!PAGE && sizeof(T) == 8) {
+    if (b > 10 && b < 48 && P.nnz * 8 >= kMemoryBytes)
+      for (; m0 + 8 < b; m0 += 16)
+        sddmm_panel<T, PR, NCH, PAGE, RS, kHold>(P, rd, m0, xbytes, xs, ring, ra);
+  }
+  for (; m0 < b; m0 += 16) {
     const int n = sizeof(T) == 8 ? (b - m0 + 3) / 4 : b - m0;
     if (n == 1)
       sddmm_panel<T, PR, NCH, PAGE, RS, -1>(P, rd, m0, xbytes, xs, ring, ra);
@@ -2776,19 +2827,16 @@ hipError_t launch_pack(const PackParams &p, const void *src, int src_dtype, hipS
   return hipGetLastError();
 }
 
-// Outputs in graph order take the ring where they are too large for the 256 MB
-// Infinity Cache; us straight from the accumulators and through the ring: FP32,
+// Outputs in graph order take the ring where they go to memory; us straight from the accumulators and through the ring: FP32,
 // 32 right-hand sides, b = 8 (250 MB) 196/174, b = 4/9 (205 MB) 217/188, b =
 // 1/4/9 (142 MB) 114/133, b = 5 (122 MB) 99/124; FP64, 16, b = 4/9 (410 MB)
 // 268/256, b = 1/4/9 (283 MB) 201/194, b = 8 (150 MB) 49/70, 1,000 rows of b =
 // 5 12/19.  FP64 beyond 32 right-hand sides never: b = 8, 48, 500 MB 367/403.
-constexpr int64_t kRingBytes = 192 << 20;
-
 template <typename T, int PR, int NCH>
 void launch_sddmm_tiles(const SddmmParams<T> &p, dim3 grid, uint32_t xbytes, hipStream_t s) {
   if (p.page_out)
     hipLaunchKernelGGL((k_sddmm<T, PR, NCH, true, 256>), grid, dim3(kThreads), 0, s, p, xbytes);
-  else if (NCH == 1 && p.nnz * (int64_t)sizeof(T) >= kRingBytes)
+  else if (NCH == 1 && p.nnz * (int64_t)sizeof(T) >= kMemoryBytes)
     hipLaunchKernelGGL((k_sddmm<T, PR, NCH, false, NCH == 1 ? 512 : 1>), grid, dim3(kThreads), 0, s, p, xbytes);
   else
     hipLaunchKernelGGL((k_sddmm<T, PR, NCH, false, 1>), grid, dim3(kThreads), 0, s, p, xbytes);

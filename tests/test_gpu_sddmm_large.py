@@ -49,11 +49,11 @@ def check(b, rp, ci, prec, counts, least):
 
 
 # widths that the ring holds beside panels that it does not (b = 11 with a
-# block of 12, b above 12), and single columns
-@pytest.mark.parametrize("prec,n", [("fp64", 7000), ("fp32", 14000)])
+# block of 12, b above 12), panels of more than 16 rows, and single columns
+@pytest.mark.parametrize("prec,n", [("fp64", 4500), ("fp32", 9000)])
 def test_graph_order_through_the_ring(prec, n):
-    b, rp, ci = graph(n, 45, (1, 2, 3, 4, 5, 8, 9, 10, 11, 12, 13), 3)
-    check(b, rp, ci, prec, (1, 7, 16, 32), 192 << 20)
+    b, rp, ci = graph(n, 45, (1, 2, 3, 4, 5, 8, 9, 10, 11, 12, 13, 13, 16, 17, 33), 3)
+    check(b, rp, ci, prec, (1, 7, 16, 32, 33, 64), 192 << 20)
 
 
 def test_ring_with_narrow_panels_beside_wide_ones():
