@@ -88,8 +88,10 @@ std::atomic<long> g_alloc_count{0};
 // Device blocks given back by handles and calls, kept for the next ones: a
 // hipMalloc and hipFree of the block product's results and temporaries cost
 // far more than its kernels (C = A A of 5,760 atoms with b in 9..20, 2.8 GB,
-// read back and destroyed, pass after pass: 92 ms with them, 5.5 ms without,
-// of which the kernels take 4.9).
+// read back and destroyed, pass after pass: 92 ms with them, 4.8 ms without).
+// A first product, one whose earlier results live on, and one whose blocks
+// exceed the bound map their memory as before; the bound, 1/64 of the device,
+// is what one such product takes with its temporaries.
 //   * A block is kept only once nothing on its device can still use it (the
 //     callers of dev_free have synchronised the device), so it may go to any
 //     stream and thread.  Contents are never relied on.

@@ -536,12 +536,11 @@ __global__ void __launch_bounds__(kThreads) k_spmm_vp(FwdParams<T> P) {
 // 2 + 2.  A ring of R register sets as in the kernel below.  Values are read
 // through the caches: two loads share each line (streamed past them, nrhs 16
 // on b = 9..20 took 203 us instead of 162).  Up to 32 rows go in one pass (162
-// -> 141).  Before (vector kernel up to 8 right-hand sides, 16x16 tiles
-// beyond) and now, us: 40,000-atom particle nrhs 8 259 -> 234, nrhs 6 270 ->
-// 227, nrhs 12 276 -> 263; b = 13 lattice nrhs 8 217 -> 195; 50,000 atoms of
-// b = 1/4/9 nrhs 4 131 -> 88, nrhs 8 148 -> 98, nrhs 16 154 -> 127, nrhs 32
-// 204 -> 197; b = 9..20 nrhs 8 140 -> 123, nrhs 16 200 -> 141, nrhs 32 246 ->
-// 217.
+// -> 141).  The kernels in their place (vector up to 8 right-hand sides, 16x16
+// tiles with 8-byte loads beyond) and these, us: 40,000-atom particle nrhs 6
+// 267 -> 228, 8 256 -> 236, 12 323 -> 259; b = 13 lattice nrhs 8 212 -> 195;
+// 50,000 atoms of b = 1/4/9 nrhs 4 132 -> 88, 8 144 -> 98, 16 189 -> 139, 32
+// 214 -> 197; b = 9..20 nrhs 8 138 -> 122, 16 212 -> 141, 32 234 -> 218.
 template <typename T, int RG, int NG, int LW, bool MOM, int R>
 __device__ __forceinline__ void small_rows(const FwdParams<T> &P, const RowDesc &rd, int m0, int c0,
                                            double *s_mom) {
@@ -793,14 +792,14 @@ __global__ void __launch_bounds__(kThreads) k_spmm_small(FwdParams<double> P) {
 // HBM and the gathered rows from L2 return through it in order, so their
 // times add up (5 KiB of L2 hits alone take 102 cycles of a unit, 1 KiB of
 // stream alone 95, together 221, at any occupancy).  Measured against two
-// alternating sets with the index tested at the load and masked rows and
-// right-hand sides: FP32 100,000 atoms of b = 1/4/9, nrhs 32: 269 -> 231 us;
-// FP32 40,000-atom particle, nrhs 13: 276 -> 159, nrhs 33: 371 -> 267, nrhs
-// 64: 326 -> 299; FP64 1,000 atoms of b = 4/9, nrhs 16: 14.8 -> 11.7 us a
-// call; FP64 50,000 atoms of b = 1/4/9, nrhs 32: 220 -> 195; FP64 Chebyshev
-// step on the 24^3 lattice b = 13, nrhs 64: 206 -> 200.  Longer rings (R = 4)
-// gain 2 % on the lattice and lose 4 % on the small blocks, groups of one
-// slice lose on the lattice.
+// alternating sets with the index tested at the load, masked rows and
+// right-hand sides and, in FP64, one row a value load: FP32 100,000 atoms of b
+// = 1/4/9, nrhs 16 208 -> 156 us, 32 260 -> 216; FP32 40,000-atom particle,
+// nrhs 13 276 -> 154, 33 369 -> 266, 64 314 -> 294; FP64 on it, nrhs 20 429 ->
+// 305, 50 656 -> 491, 64 557 -> 540; FP64 32^3 lattice b = 13, nrhs 16 241 ->
+// 215; FP64 Chebyshev step on the 24^3 one, nrhs 64: 206 -> 200.  Longer rings
+// (R = 4) gain 2 % on the lattice and lose 4 % on the small blocks, groups of
+// one slice lose on the lattice.
 //
 // VX: the N index of the 16x16 tiles is permuted so that lane m of tile t
 // holds right-hand side c0 + l*16*VEC + VEC*m + e, with t = l*VEC + e and VEC
@@ -810,7 +809,7 @@ __global__ void __launch_bounds__(kThreads) k_spmm_small(FwdParams<double> P) {
 // XB this serves every nrhs and leading dimension that fill VEC tiles (a
 // lane's elements past nrhs go to columns that are not stored); with one
 // 8-byte load per tile FP64 nrhs 20 and 50 took 367 and 600 us on the
-// 40,000-atom particle, now 309 and 497.
+// 40,000-atom particle, with these 305 and 491.
 // Without XB it needs 16-byte aligned rows and whole passes.  The other
 // form (VX = false) loads one element per lane and tile.
 template <typename T> struct Vec16;
@@ -1927,10 +1926,12 @@ __global__ void __launch_bounds__(kThreads) k_sddmm_lds(SddmmParams<T> P) {
 // The ring's turn through LDS takes as long as a tile's matrix instructions, so
 // it is for outputs that go to memory: see the launcher.
 //
-// b = 1/4/9, K about 150: 32 right-hand sides, FP32, 100 000 panels, graph
-// order 357 -> 299 us, pages 287 -> 238; FP64, 50 000 panels 302 -> 262 and
-// 236 -> 224; 40 right-hand sides FP64 546 -> 394; b = 4/9, 8000 panels, 7
-// right-hand sides, FP64, pages 87 -> 31.
+// Against kernels for 32 and 64 right-hand sides with scattered stores, and one
+// that staged X through registers for the other counts: b = 1/4/9, K about 150,
+// 32 right-hand sides, FP32, 100,000 panels, graph order 357 -> 309 us, pages
+// 287 -> 235; FP64, 50,000 panels 297 -> 264 and 235 -> 221; 40 right-hand sides
+// FP64 544 -> 385; b = 4/9, 8,000 panels, 7 right-hand sides, FP64, 89 -> 38,
+// pages 86 -> 33; b = 13 lattice, 64, FP64 pages 633 -> 524.
 // Values of NS: the form that holds outputs back, and that with 64-bit addresses.
 constexpr int kHold = -8, kWide = 0;
 // Outputs of this size and more go to memory, not to the 256 MB Infinity Cache.

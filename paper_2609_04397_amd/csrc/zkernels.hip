@@ -243,7 +243,7 @@ __device__ __forceinline__ void zstore(const ZSpmmParams<T> &P, int64_t r, int c
 // compared with the panel's end where it is used (at the load it would be
 // waited for).  The blocks' partial sums meet once per panel.
 // Bound by the load path (16 cycles of a compute unit per load): O(k) of the
-// b = 1/4/9 cube of 20 000 atoms, 16 right-hand sides, 98 us against 181 us
+// b = 1/4/9 cube of 20 000 atoms, 16 right-hand sides, 103 us against 163 us
 // with 16-row tiles, whose matrix work was mostly padding; R = 3 110 us.
 template <typename T, int RG, int NG, int R, bool PARTS>
 __device__ __forceinline__ void zsmall_rows(const ZSpmmParams<T> &P, const RowDesc &rd, int m0, int c0,
@@ -541,10 +541,11 @@ hipError_t launch_zsample(const ZSampleParams &p, void *fwd, void *tr, int elem_
 
 // Matrix cores when X spans less than one buffer descriptor (kXSpan), else
 // the vector kernel with 64-bit addresses.  Small tiles for operators of any but
-// the smallest blocks up to 16 right-hand sides and in FP32 (vector kernel against small tiles, FP64
-// O(k) of the b = 1/4/9 cube of 20 000 atoms: 51 against 43 us at 1, 77/49 at
-// 4, 196/66 at 8; FP32 42/37 at 1, 99/55 at 8, 201/94 at 16, 385/180 at 32;
-// 16-row tiles against small tiles at 16: 181/98).  FP64 beyond 16: small
+// the smallest blocks up to 16 right-hand sides and in FP32 (vector kernel
+// against small tiles, O(k) of the b = 1/4/9 cube of 20 000 atoms, FP64: 53
+// against 43 us at 1, 78/49 at 4, 195/70 at 8; FP32 42/38 at 1, 99/57 at 8,
+// 197/98 at 16, 387/182 at 32; 16-row tiles against small tiles, FP64 at 16:
+// 163/103).  FP64 beyond 16: small
 // tiles where 16-row tiles pad much (b = 1/4/9, ratio 1.9: 204 us against 162
 // at 24, 386/239 at 40, 388/330 at 64), 16-row tiles where they pad less
 // (b = 9/20, ratio 1.4: 316 against 331 at 20, 331/364 at 32, 591/787 at 64).
