@@ -1653,8 +1653,9 @@ __global__ void __launch_bounds__(kThreads) k_refresh(const PageRec *rec, int64_
   if (u0 >= nnzb) return;
   const int lane = threadIdx.x & 63;
   const int nb = (int)min((int64_t)kPackRun, nnzb - u0);
-  PageRec r{};
-  if (lane < nb) r = rec[u0 + lane];
+  // every lane holds a record: one filled in part of the lanes goes through LDS,
+  // whose address then needs the dispatch packet in host memory (13 us a call)
+  const PageRec r = rec[u0 + min(lane, nb - 1)];
   transpose_run<T>(r, tab_all + wave_id() * kPackRun, nb, lane, 0, 1, src, dst);
 }
 
