@@ -2829,11 +2829,15 @@ hipError_t launch_pack(const PackParams &p, const void *src, int src_dtype, hipS
   return hipGetLastError();
 }
 
-// Outputs in graph order take the ring where they go to memory; us straight from the accumulators and through the ring: FP32,
-// 32 right-hand sides, b = 8 (250 MB) 196/174, b = 4/9 (205 MB) 217/188, b =
-// 1/4/9 (142 MB) 114/133, b = 5 (122 MB) 99/124; FP64, 16, b = 4/9 (410 MB)
-// 268/256, b = 1/4/9 (283 MB) 201/194, b = 8 (150 MB) 49/70, 1,000 rows of b =
-// 5 12/19.  FP64 beyond 32 right-hand sides never: b = 8, 48, 500 MB 367/403.
+// Outputs in graph order take the ring where they go to memory; us straight
+// from the accumulators and through the ring: FP32, 32 right-hand sides, b = 8
+// (250 MB) 196/174, b = 4/9 (205 MB) 217/188, b = 1/4/9 (142 MB) 114/133, b = 5
+// (122 MB) 99/124; FP64, 16, b = 4/9 (410 MB) 268/256, b = 1/4/9 (283 MB)
+// 201/194, b = 8 (150 MB) 49/70, 1,000 rows of b = 5 12/19.  FP64 beyond 32
+// right-hand sides never: b = 8, 48, 500 MB 367/403; 64, b = 1/4/9, 640 MB
+// 774/819, b = 4/9, 660 MB 786/803 (its LDS, held until a workgroup's last wave
+// ends, costs the panels that do not use it as much).  Only 9 rows beside
+// blocks of 13 gain there (b = 9/13, 490 MB 404/389; b = 13/9/1, 950 MB 772/748).
 template <typename T, int PR, int NCH>
 void launch_sddmm_tiles(const SddmmParams<T> &p, dim3 grid, uint32_t xbytes, hipStream_t s) {
   if (p.page_out)
